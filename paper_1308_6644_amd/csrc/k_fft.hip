@@ -11,6 +11,8 @@
 // [N''/2, 3N''/2), and only the support rows/columns [s0, s0 + L),
 // L = N'' + 16, are ever stored.  Row passes over the fine grid are
 // instantiated at N''; the column passes go between N'' and N'.
+#include <algorithm>
+
 #include "group.h"
 #include "launch.h"
 
@@ -44,6 +46,24 @@ struct ColCfg {
 };
 
 __device__ __forceinline__ bool in_band(int k, int lo, int hi) { return k >= lo && k <= hi; }
+
+// Column passes launch the strips of C columns (of n, frequency k_x at column
+// k_x + n/2) that meet the band of Eq. 4, and no others: the first one and
+// their number.  The column range dealt to the XCDs is then the band's own.
+// (With every strip launched and the ones outside the band leaving at once,
+// the band, a run of consecutive strips, sat on a few of the eight XCDs:
+// N' = 2048 with half the columns in band 36.6 us, N' = 8192 with 2020 in
+// band 284 us, one launch.)
+// (An explicit band that is empty along y alone may reach outside the n
+// columns along x: both ends are clamped to them.)
+__host__ __device__ __forceinline__ int band_strip0(const GridGeom& g, int n, int C) {
+  const int a = g.kxlo + n / 2;
+  return (a < 0 ? 0 : a) / C;
+}
+static int band_strips(const GridGeom& g, int n, int C) {
+  const int a0 = std::max(g.kxlo + n / 2, 0), a1 = std::min(g.kxhi + n / 2, n - 1);
+  return a0 > a1 ? 0 : a1 / C - a0 / C + 1;
+}
 
 // float64 square root from the hardware seed (v_rsq_f64) refined by Newton
 // steps: each step squares the relative error, so two steps from the ~2^-23
@@ -154,10 +174,8 @@ __device__ __forceinline__ void t1_cols_body(const ColArgs& a, int bid, int nbid
   using Cfg = Col2Cfg<LOGN, LOGNP>;
   constexpr int C = Cfg::C, NT = Cfg::NT;
   extern __shared__ float2 s[];
-  const int strip = xcd_remap(bid, nbid);
-  const int a0 = strip * C;
+  const int a0 = (band_strip0(g, NPF, C) + xcd_remap(bid, nbid)) * C;
   const int kx0 = a0 - NPF / 2;
-  if (kx0 + C - 1 < g.kxlo || kx0 > g.kxhi) return;  // whole strip outside the band
   float2* twf = s + Cfg::DATA;
   float2* twp = twf + Tw2<LOGN>::SIZE;
   load_tw2<LOGN, NT>(twf, tw_for(twall, LOGN));
@@ -289,10 +307,8 @@ __device__ __forceinline__ void t2_cols_body(const ColArgs& a, int bid, int nbid
   using Cfg = Col2Cfg<LOGNP, LOGN>;
   constexpr int C = Cfg::C, NT = Cfg::NT;
   extern __shared__ float2 s[];
-  const int strip = xcd_remap(bid, nbid);
-  const int a0 = strip * C;
+  const int a0 = (band_strip0(g, NP, C) + xcd_remap(bid, nbid)) * C;
   const int kx0 = a0 - NP / 2;
-  if (kx0 + C - 1 < g.kxlo || kx0 > g.kxhi) return;
   float2* twp = s + Cfg::DATA;
   float2* twf = twp + Tw2<LOGNP>::SIZE;
   load_tw2<LOGNP, NT>(twp, tw_for(twall, LOGNP));
@@ -396,10 +412,8 @@ k_t3_cols(const float2* __restrict__ T, float2* __restrict__ V, GridGeom g, Spec
   using Cfg = T3Cfg<LOGN>;
   constexpr int C = Cfg::C, NT = Cfg::NT;
   extern __shared__ float2 s[];
-  const int strip = xcd_remap(blockIdx.x, gridDim.x);
-  const int a0 = strip * C;
+  const int a0 = (band_strip0(g, NP, C) + xcd_remap((int)blockIdx.x, (int)gridDim.x)) * C;
   const int kx0 = a0 - NP / 2;
-  if (kx0 + C - 1 < g.kxlo || kx0 > g.kxhi) return;  // whole strip outside the band
   float2* twf = s + Cfg::DATA;
   load_tw2<LOGN, NT>(twf, tw_for(twall, LOGN));
   const int L = g.L, s0 = g.s0;
@@ -548,16 +562,16 @@ template <int LPF, int LP>
 static hipError_t t1_cols_at(const float2* T, float2* V, const GridGeom& g, const Spectral& sp, const float2* tw,
                              hipStream_t st) {
   using Cfg = Col2Cfg<LPF + 1, LP>;
-  return launch_or_record<ColArgs, t1_cols_body<LPF, LP>, Cfg::NT>(ColArgs{T, V, g, sp, tw}, (1 << LPF) / Cfg::C,
-                                                                   Cfg::LDS, st);
+  return launch_or_record<ColArgs, t1_cols_body<LPF, LP>, Cfg::NT>(
+      ColArgs{T, V, g, sp, tw}, band_strips(g, 1 << LPF, Cfg::C), Cfg::LDS, st);
 }
 
 template <int LPF, int LP>
 static hipError_t t2_cols_at(const float2* T, float2* V, const GridGeom& g, const Spectral& sp, const float2* tw,
                              hipStream_t st) {
   using Cfg = Col2Cfg<LP, LPF + 1>;
-  return launch_or_record<ColArgs, t2_cols_body<LPF, LP>, Cfg::NT>(ColArgs{T, V, g, sp, tw}, (1 << LP) / Cfg::C,
-                                                                   Cfg::LDS, st);
+  return launch_or_record<ColArgs, t2_cols_body<LPF, LP>, Cfg::NT>(
+      ColArgs{T, V, g, sp, tw}, band_strips(g, 1 << LP, Cfg::C), Cfg::LDS, st);
 }
 
 template <int LP, bool T1>
@@ -645,7 +659,8 @@ hipError_t launch_t3_cols(int logNp, const float2* T, float2* V, GridGeom g, Spe
     using Cfg = T3Cfg<LP + 1>;                                                           \
     hipError_t e = set_lds(k_t3_cols<LP>, Cfg::LDS);                                     \
     if (e != hipSuccess) return e;                                                       \
-    const int grid = (1 << LP) / Cfg::C;                                                 \
+    const int grid = band_strips(g, 1 << LP, Cfg::C);                                    \
+    if (grid <= 0) return hipSuccess;                                                    \
     hipLaunchKernelGGL(k_t3_cols<LP>, dim3(grid), dim3(Cfg::NT), Cfg::LDS, st, T, V, g, sp, tw); \
   }
   NUASM_DISPATCH_NP(logNp, CALL)
