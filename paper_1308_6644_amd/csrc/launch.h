@@ -11,6 +11,7 @@ namespace nuasm {
 constexpr int kTile = 32;        // default fine cells per bin side (32 or 64)
 constexpr int kPad = 8;          // support margin: taps reach w/2 <= 8 cells past the window
 constexpr int kChunk = 2048;       // default max records per interpolation workgroup
+constexpr int kSpreadMinChunk = 256;  // one sub-batch of the matrix-core spreading
 constexpr int kSpreadChunk = 1792; // default max records per spreading workgroup
 // Spreading chunk sizes the kernel is instantiated for: whole sub-batches of
 // 448 records (w <= 8) or 256 (w > 8); `small` is about half the default.

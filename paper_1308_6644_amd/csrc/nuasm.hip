@@ -272,6 +272,8 @@ struct PointSet {
   int64_t M = 0;
   bool ready = false;
   bool synced = false;
+  int sp_chunk = kSpreadChunk;  // records per spreading / interpolation chunk of the bound points
+  int ip_chunk = kChunk;
   int exact_sp = 0, exact_ip = 0, exact_multi = 0, exact_slots = 0;
   // a uniform grid bound with nuasm_set_grid_points (no records, no binning)
   bool grid = false;
@@ -309,6 +311,8 @@ struct nuasm_plan_s {
   bool sp_small = false;  // spreading chunks of about half the default size
   int sp_chunk = kSpreadChunk;
   int ip_chunk = kChunk;
+  bool sp_auto = true;    // chunk sizes not tuned: they follow the point count (set_chunks)
+  bool ip_auto = true;
   int bin_ppw = 0;        // points per binning workgroup, 0 = automatic
   int sp_method = 0;      // spreading: 0 automatic, 1 register gather, 2 matrix cores
   int nsets = 1;
@@ -654,6 +658,31 @@ void set_tile(nuasm_plan_s* pl, int tile) {
   pl->bgeom.tile_log = pl->tile_log;
 }
 
+// Chunk sizes of a point set of M points.  The default sizes suit counts that
+// fill the chip; below that, bins of a few thousand records would leave most
+// CUs idle while a few workgroups walk their sub-batches one after the other
+// (30011 clustered points on N' = 512, tol 1e-3: spreading 31 us with
+// 1792-record chunks, 7.5 with 256; interpolation 6.8 -> 3.9), so untuned
+// plans cut the bins finer: down to one sub-batch, but never to more than 2047
+// possible partial tiles (8 M / chunk), the bound that an allocation-free
+// execute has to meet.  Above 458 000 points that is the default size.
+// Interpolation likewise, down to 512 records and at most 1024 chunks.  Plans
+// on a caller's workspace keep the default sizes their capacity was computed
+// from, and so do deterministic plans (their sums follow the chunks), the
+// 64 x 64 bins and the register-gather spreading.
+constexpr int64_t kAutoChunks = 1024;
+
+void set_chunks(const nuasm_plan_s* pl, PointSet& q, int64_t M) {
+  q.sp_chunk = pl->sp_chunk;
+  q.ip_chunk = pl->ip_chunk;
+  if (pl->ws || stable_bins(pl) || pl->tile != kTile || pl->sp_method == 1) return;
+  auto fit = [](int64_t need, int64_t lo, int64_t hi) {
+    return (int)std::min(hi, std::max(lo, (need + 255) / 256 * 256));
+  };
+  if (pl->sp_auto) q.sp_chunk = fit((8 * M + 2046) / 2047, kSpreadMinChunk, kSpreadChunk);
+  if (pl->ip_auto) q.ip_chunk = fit((4 * M + kAutoChunks - 1) / kAutoChunks, 512, kChunk);
+}
+
 nuasm_status ensure_points_capacity(nuasm_plan_s* pl, PointSet& q, int64_t M) {
   if (pl->ws) {
     if (M <= q.rec_cap) return NUASM_OK;
@@ -701,7 +730,8 @@ nuasm_status ensure_points_capacity(nuasm_plan_s* pl, PointSet& q, int64_t M) {
     HIP_TRY(dalloc(pl, &q.hoff, (size_t)q.hist_rows * (pl->T + 1)), "hipMalloc(bin offsets)");
   }
   HIP_TRY(dalloc(pl, &q.recs, (size_t)(4 * cap)), "hipMalloc(records)");
-  q.chunk_cap = pl->T + (4 * cap) / std::min(pl->sp_chunk, pl->ip_chunk) + 1;  // covers both chunk tables
+  // covers both chunk tables, at any point count up to cap
+  q.chunk_cap = pl->T + std::max((4 * cap) / std::min(pl->sp_chunk, pl->ip_chunk), kAutoChunks) + 1;
   HIP_TRY(dalloc(pl, &q.sp_chunks, (size_t)q.chunk_cap), "hipMalloc(chunks)");
   HIP_TRY(dalloc(pl, &q.ip_chunks, (size_t)q.chunk_cap), "hipMalloc(chunks)");
   q.rec_cap = cap;
@@ -714,7 +744,7 @@ nuasm_status ensure_points_capacity(nuasm_plan_s* pl, PointSet& q, int64_t M) {
 // records, so fewer than 8 M / chunk slots are ever used.
 int64_t scratch_tiles_needed(const nuasm_plan_s* pl, const PointSet& q) {
   if (q.synced) return q.exact_slots;
-  return std::min<int64_t>(q.chunk_cap, (8 * q.M) / pl->sp_chunk + 1);
+  return std::min<int64_t>(q.chunk_cap, (8 * q.M) / q.sp_chunk + 1);
 }
 
 nuasm_status ensure_scratch(nuasm_plan_s* pl, PointSet& q) {
@@ -751,13 +781,13 @@ nuasm_status point_status(const PointSet& q, int which) {
 // Grid sizes of the point kernels: the exact chunk counts once a set_points
 // has synchronised, else upper bounds (surplus workgroups exit at once).
 int sp_grid(const nuasm_plan_s* pl, const PointSet& q) {
-  return q.synced ? q.exact_sp : (int)std::min<int64_t>(q.chunk_cap, pl->T + (4 * q.M) / pl->sp_chunk + 1);
+  return q.synced ? q.exact_sp : (int)std::min<int64_t>(q.chunk_cap, pl->T + (4 * q.M) / q.sp_chunk + 1);
 }
 int ip_grid(const nuasm_plan_s* pl, const PointSet& q) {
-  return q.synced ? q.exact_ip : (int)std::min<int64_t>(q.chunk_cap, pl->T + (4 * q.M) / pl->ip_chunk + 1);
+  return q.synced ? q.exact_ip : (int)std::min<int64_t>(q.chunk_cap, pl->T + (4 * q.M) / q.ip_chunk + 1);
 }
 int multi_grid(const nuasm_plan_s* pl, const PointSet& q) {
-  return q.synced ? q.exact_multi : (int)std::min<int64_t>(pl->T, (4 * q.M) / pl->sp_chunk + 1);
+  return q.synced ? q.exact_multi : (int)std::min<int64_t>(pl->T, (4 * q.M) / q.sp_chunk + 1);
 }
 
 // The rejected points' indices are stored downwards from the end of the
@@ -773,6 +803,7 @@ nuasm_status bind_points(nuasm_plan_s* pl, PointSet& q, int64_t M, const double*
   q.grid = false;
   nuasm_status s = ensure_points_capacity(pl, q, M);
   if (s != NUASM_OK) return s;
+  set_chunks(pl, q, M);
   hipStream_t st = pl->stream;
   {
     int ppw = 0, G = 0;
@@ -785,7 +816,7 @@ nuasm_status bind_points(nuasm_plan_s* pl, PointSet& q, int64_t M, const double*
       // column scan, then bin scan; with no points (G = 0) they write zero
       // totals and empty-bin chunk tables
       const BinScanOut so{q.cursor, q.sp_chunks, q.sp_first, q.sp_n, q.multi, q.ip_chunks, q.nch,
-                          q.bin_pre, q.wg_sum, pl->sp_chunk, pl->ip_chunk};
+                          q.bin_pre, q.wg_sum, q.sp_chunk, q.ip_chunk};
       {
         StageScope sc(pl, NUASM_STAGE_BIN_COLSCAN);
         HIP_TRY(launch_bin_colscan(q.hist, M > 0 ? G : 0, pl->T, q.hoff, q.counts, so, st), "launch bin_colscan");
@@ -1337,12 +1368,14 @@ nuasm_status nuasm_plan_set_tuning(nuasm_plan pl, const nuasm_tuning* t) {
   // request below the default takes the small one
   const int small = spread_nsub(pl->w, true) * spread_subbatch(pl->w);
   struct Sizes {
-    bool sp_small;
+    bool sp_small, sp_auto, ip_auto;
     int sp_chunk, ip_chunk, bin_ppw, sp_method, tile;
   };
-  const Sizes old{pl->sp_small, pl->sp_chunk, pl->ip_chunk, pl->bin_ppw, pl->sp_method, pl->tile};
+  const Sizes old{pl->sp_small, pl->sp_auto, pl->ip_auto, pl->sp_chunk, pl->ip_chunk, pl->bin_ppw, pl->sp_method, pl->tile};
   Sizes nw;
   nw.sp_small = t->spread_chunk != 0 && t->spread_chunk < kSpreadChunk;
+  nw.sp_auto = t->spread_chunk == 0;
+  nw.ip_auto = t->interp_chunk == 0;
   nw.sp_chunk = nw.sp_small ? small : kSpreadChunk;
   nw.ip_chunk = t->interp_chunk != 0 ? t->interp_chunk : kChunk;
   nw.bin_ppw = t->bin_range_points;
@@ -1350,6 +1383,8 @@ nuasm_status nuasm_plan_set_tuning(nuasm_plan pl, const nuasm_tuning* t) {
   nw.tile = new_tile;
   auto apply = [&](const Sizes& z) {
     pl->sp_small = z.sp_small;
+    pl->sp_auto = z.sp_auto;
+    pl->ip_auto = z.ip_auto;
     pl->sp_chunk = z.sp_chunk;
     pl->ip_chunk = z.ip_chunk;
     pl->bin_ppw = z.bin_ppw;
