@@ -352,7 +352,9 @@ nuasm_status nuasm_rs_direct(int64_t M1, const double* x1_dev, const double* y1_
                              double ox, double oy, void* out_dev, void* hip_stream);
 
 /* Per-kernel device timing with HIP events recorded on the plan's stream
- * around each kernel launch (off by default).  Stages, one kernel each: */
+ * around each kernel launch (off by default).  While it is on, set_points
+ * runs its four stages as four launches (off, it fuses them: same records and
+ * tables).  Stages, one kernel each: */
 #define NUASM_STAGE_BIN_HIST 0     /* set_points: per-range bin histograms */
 #define NUASM_STAGE_BIN_COLSCAN 1  /* set_points: offsets across ranges, per-bin prefixes */
 #define NUASM_STAGE_BIN_SCAN 2     /* set_points: bin bases and chunk tables */

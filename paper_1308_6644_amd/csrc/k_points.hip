@@ -154,12 +154,16 @@ __device__ __forceinline__ int size_class(int c, int chunk) {
   return c >= chunk ? 3 : 2 * c >= chunk ? 2 : 8 * c >= chunk ? 1 : 0;
 }
 
-__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(v, o, 64);
-    if (lane >= o) v += t;
-  }
+// Inclusive scan over the wave in six DPP additions: shifts by 1, 2, 4 and 8
+// inside the rows of 16 lanes, then the last lane of row 0 (and 2) broadcast
+// into row 1 (and 3), and of row 1 into rows 2 and 3.
+__device__ __forceinline__ int wave_incl_scan(int v, int) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
   return v;
 }
 
@@ -222,7 +226,8 @@ __device__ __forceinline__ void bin_colscan_body(const ColscanArgs& a, int bid, 
       if (wv == kColWaves - 1) total[b] = run;
     }
   }
-  if (wv != kColWaves - 1) return;
+  // (bin_pre null: the scatter scans the totals itself)
+  if (wv != kColWaves - 1 || !so.bin_pre) return;
   // the workgroup's 64 bins: per-bin exclusive prefixes and the sums
   int c = 0;
   if (b < T) {
@@ -439,6 +444,275 @@ __device__ __forceinline__ void bin_scatter_body(const BinArgs& a, int bid, int)
         }
     }
   }
+}
+
+// ------------------------------------------------- binning in three launches
+// The default binning: histogram, column scan, and a scatter whose workgroups
+// each scan the bin totals themselves (17 KB at T = 4225, out of L2), so that
+// no launch is needed between the column scan and the scatter; one more
+// workgroup per 1024 bins, dispatched first, writes the bin bases and the
+// chunk tables that the later kernels read.  Taken up to the bin count whose cursors fit the
+// scatter's LDS.  2^20 points, 4225 bins: column scan + bin scan + scatter
+// 7.3 + 4.7 + 16.9 us, now column scan + scatter 5.3 + 19.4 us and one gap
+// between launches less.
+
+__host__ __device__ constexpr int bin_table_workgroups(int T) { return (T + kBinThreads - 1) / kBinThreads; }
+
+// Bin bases and chunk tables of the bins 1024 u .. 1024 u + 1023, a thread
+// each, for u in [u0, u1), by one workgroup: it scans the totals of all bins
+// (their wave sums meet in LDS) and then writes its own.  count(b) gives a
+// bin's records, base(b, rec0) receives its first record.
+template <class Count, class Base>
+__device__ __forceinline__ void bin_tables(int T, const BinScanOut& so, int rejected, int u0, int u1,
+                                           const Count& count, const Base& base) {
+  constexpr int NW = kBinThreads / 64, RMAX = kScatterCursorBytes / 4 / kBinThreads;
+  __shared__ int part[kWgVals][RMAX * NW];
+  const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int rounds = (T + kBinThreads - 1) / kBinThreads;
+  const int spc = so.sp_chunk, ipc = so.ip_chunk;
+  int c = 0, nsp = 0, nip = 0, ksp = 0, kip = 0;
+  int v[kWgVals];
+  auto values = [&](int b) {
+    const bool valid = b < T;
+    c = valid ? count(b) : 0;
+    nsp = valid ? spread_chunks(c, spc) : 0;
+    nip = (c + ipc - 1) / ipc;
+    ksp = size_class(c, spc);
+    kip = size_class(c, ipc);
+    v[kWgRec] = c;
+    v[kWgMulti] = nsp > 1 ? 1 : 0;
+    v[kWgSlot] = nsp > 1 ? nsp : 0;
+#pragma unroll
+    for (int k = 0; k < kClasses; ++k) {
+      v[kWgSp + k] = ksp == k ? nsp : 0;
+      v[kWgIp + k] = kip == k ? nip : 0;
+    }
+  };
+  // (a wave without bins of its own has nothing to scan)
+  for (int u = 0; u < rounds; ++u) {
+    if (u * kBinThreads + wv * 64 >= T) {
+      if (lane < kWgVals) part[lane][u * NW + wv] = 0;
+      continue;
+    }
+    values(u * kBinThreads + t);
+#pragma unroll
+    for (int i = 0; i < kWgVals; ++i) {
+      const int inc = wave_incl_scan(v[i], lane);
+      if (lane == 63) part[i][u * NW + wv] = inc;
+    }
+  }
+  __syncthreads();
+  for (int u = u0; u < u1; ++u) {
+    const int b = u * kBinThreads + t;
+    if (u * kBinThreads + wv * 64 >= T) continue;
+    values(b);
+    int tot[kWgVals];
+#pragma unroll
+    for (int i = 0; i < kWgVals; ++i) {
+      int pre = 0;
+      tot[i] = 0;
+      for (int k = 0; k < rounds * NW; k += 64) {
+        const int x = k + lane < rounds * NW ? part[i][min(k + lane, RMAX * NW - 1)] : 0;
+        const int inc = wave_incl_scan(x, lane);
+        const int before = u * NW + wv - k;  // entries of this step ahead of the wave's own
+        if (before > 0) pre += __builtin_amdgcn_readlane(inc, min(before, 64) - 1);
+        tot[i] += __builtin_amdgcn_readlane(inc, 63);
+      }
+      v[i] = wave_incl_scan(v[i], lane) - v[i] + pre;
+    }
+    int nsp_all = 0, nip_all = 0, first = 0, ifirst = 0;
+#pragma unroll
+    for (int k = kClasses - 1; k >= 0; --k) {  // largest class first
+      if (ksp == k) first = nsp_all + v[kWgSp + k];
+      if (kip == k) ifirst = nip_all + v[kWgIp + k];
+      nsp_all += tot[kWgSp + k];
+      nip_all += tot[kWgIp + k];
+    }
+    if (b == 0) {
+      so.nch[0] = nsp_all;
+      so.nch[1] = nip_all;
+      so.nch[2] = tot[kWgRec];
+      so.nch[3] = tot[kWgMulti];
+      so.nch[4] = rejected;
+      so.nch[5] = tot[kWgSlot];
+    }
+    if (b < T) {
+      const int rec0 = v[kWgRec], slot0 = v[kWgSlot];
+      base(b, rec0);
+      so.cursor[b] = rec0;
+      so.sp_first[b] = first;
+      so.sp_n[b] = nsp;
+      if (nsp > 1) so.multi[v[kWgMulti]] = b;
+      // .w: the chunk's partial-tile slot when the bin is split, else -1
+      for (int r = 0; r < nsp; ++r)
+        so.sp_chunks[first + r] = make_int4(b, rec0 + r * spc, min(spc, c - r * spc), nsp > 1 ? slot0 + r : -1);
+      for (int r = 0; r < nip; ++r)
+        so.ip_chunks[ifirst + r] = make_int4(b, rec0 + r * ipc, min(ipc, c - r * ipc), nip);
+    }
+  }
+}
+
+// The records of point j, from the write cursors in LDS.
+__device__ __forceinline__ void put_records(const PointCells& pc, const BinGeom& g, int64_t j, unsigned* sh, int T,
+                                            BinRec* __restrict__ recs, int* rej_end) {
+  if (!pc.ok) {
+    // outside the window: no record; its index is listed for the NaN outputs
+    // of a deferred range check
+    rej_end[-1 - (int)atomicAdd(&sh[T], 1u)] = (int)j;
+    return;
+  }
+  const int bx0 = pc.i0x >> g.tile_log, bx1 = g.primary_only ? bx0 : (pc.i0x + g.w - 1) >> g.tile_log;
+  const int by0 = pc.i0y >> g.tile_log, by1 = g.primary_only ? by0 : (pc.i0y + g.w - 1) >> g.tile_log;
+  for (int by = by0; by <= by1; ++by)
+    for (int bx = bx0; bx <= bx1; ++bx) {
+      const int slot = (int)atomicAdd(&sh[by * g.TX + bx], 1u);
+      const int lx = pc.i0x - (bx << g.tile_log), ly = pc.i0y - (by << g.tile_log);
+      BinRec r;
+      r.packed = (lx & 0xff) | ((ly & 0xff) << 8) | ((bx == bx0 && by == by0) ? (1 << 16) : 0);
+      r.dx = pc.dx;
+      r.dy = pc.dy;
+      r.idx = (int32_t)j;
+      recs[slot] = r;
+    }
+}
+
+// Scatter with the scan of the totals: the first bin_table_workgroups(T)
+// workgroups write the tables, each of the others the records of one range.
+__device__ __forceinline__ void bin_scatter_scan_body(const BinScatterArgs& sa, int bid, int) {
+  const BinArgs& a = sa.b;
+  const BinGeom& g = a.g;
+  const int T = g.TX * g.TX;
+  const int* __restrict__ total = sa.total;
+  extern __shared__ unsigned sh[];
+  constexpr int NW = kBinThreads / 64, NB = 8;  // bins per thread and stage
+  const int ntab = bin_table_workgroups(T);
+  if (bid < ntab) {
+    bin_tables(T, sa.so, total[T], bid, bid + 1, [&](int b) { return total[b]; }, [](int, int) {});
+    return;
+  }
+  const int range = bid - ntab;
+  const double* __restrict__ x = a.x;
+  const double* __restrict__ y = a.y;
+  __shared__ int part[NB * NW];
+  static_assert(NB * NW == 128, "a stage's wave sums are scanned two per lane");
+  const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int* myoff = a.off + (size_t)range * (T + 1);
+  const int64_t j0 = (int64_t)range * a.ppw;
+  const int64_t j1 = min(a.M, j0 + a.ppw);
+  double xv[kBinBatch], yv[kBinBatch];
+  // positions clamped into the range (never empty), so that no load sits
+  // behind a branch; points past its end are skipped where they are used
+  auto load = [&](int64_t jb) {
+#pragma unroll
+    for (int q = 0; q < kBinBatch; ++q) {
+      const int64_t j = min(jb + t + q * kBinThreads, j1 - 1);
+      xv[q] = x[j];
+      yv[q] = y[j];
+    }
+  };
+  load(j0);  // the first batch in flight with the cursor staging
+  int carry = 0;
+  for (int b0 = 0; b0 <= T; b0 += kBinThreads * NB) {
+    // rounds of 1024 bins left, entry T included.  Inside a round every load
+    // and LDS write is unconditional: a bin past T is clamped to T (whose
+    // total counts for nothing here) and its cursor written, with the same
+    // value, by several lanes
+    const int nu = (T - b0) / kBinThreads + 1;
+    int v[NB], o[NB];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      if (u >= nu) break;
+      const int b = min(b0 + t + u * kBinThreads, T);
+      v[u] = total[b];
+      o[u] = myoff[b];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      int inc = 0;
+      if (u < nu) {
+        if (b0 + t + u * kBinThreads >= T) v[u] = 0;
+        inc = wave_incl_scan(v[u], lane);
+        v[u] = inc - v[u];
+      }
+      if (lane == 63) part[u * NW + wv] = inc;
+    }
+    __syncthreads();
+    const int p0 = part[lane], p1 = part[64 + lane];
+    const int s0 = wave_incl_scan(p0, lane);
+    const int half = __builtin_amdgcn_readlane(s0, 63);
+    const int s1 = half + wave_incl_scan(p1, lane);
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      if (u >= nu) break;
+      const int k = u * NW + wv;  // exclusive sum of the waves before this one
+      const int e = __builtin_amdgcn_readlane(u < NB / 2 ? s0 - p0 : s1 - p1, k & 63);
+      const int b = min(b0 + t + u * kBinThreads, T);
+      sh[b] = (unsigned)(b < T ? carry + e + v[u] + o[u] : o[u]);
+    }
+    carry += __builtin_amdgcn_readlane(s1, 63);
+    __syncthreads();
+  }
+  for (int64_t jb = j0; jb < j1; jb += kBinThreads * kBinBatch) {
+    if (jb != j0) load(jb);
+#pragma unroll
+    for (int q = 0; q < kBinBatch; ++q) {
+      const int64_t j = jb + t + q * kBinThreads;
+      if (j >= j1) continue;
+      put_records(point_cells(xv[q], yv[q], g), g, j, sh, T, a.recs, a.rej_end);
+    }
+  }
+}
+
+// The whole binning of a small point set in one workgroup: counts in LDS, the
+// tables and bases from them, and the records.  Bound by the latency of its
+// serial steps: 4096 points on 25 bins take 11.8 us, against 4.8 + 5.6 + 3.1 +
+// 6.5 us in four launches (8.3 + 3.7 + 6 in three).  Up to kBinSmall points,
+// one range of the general path (4 points a thread), beyond which a second CU
+// would help.
+__device__ __forceinline__ void bin_small_body(const BinScatterArgs& sa, int, int) {
+  const BinArgs& a = sa.b;
+  const BinGeom& g = a.g;
+  const int T = g.TX * g.TX, t = threadIdx.x;
+  extern __shared__ unsigned sh[];
+  const int M = (int)a.M;  // <= kBinSmall, >= 1
+  constexpr int B = kBinSmall / kBinThreads;
+  double xv[B], yv[B];
+#pragma unroll
+  for (int q = 0; q < B; ++q) {
+    const int j = min(t + q * kBinThreads, M - 1);
+    xv[q] = a.x[j];
+    yv[q] = a.y[j];
+  }
+  for (int b = t; b <= T; b += kBinThreads) sh[b] = 0u;
+  __syncthreads();
+  PointCells pc[B];
+#pragma unroll
+  for (int q = 0; q < B; ++q) {
+    if (t + q * kBinThreads >= M) continue;
+    pc[q] = point_cells(xv[q], yv[q], g);
+    if (!pc[q].ok) {
+      atomicAdd(&sh[T], 1u);
+      continue;
+    }
+    const int bx0 = pc[q].i0x >> g.tile_log, bx1 = g.primary_only ? bx0 : (pc[q].i0x + g.w - 1) >> g.tile_log;
+    const int by0 = pc[q].i0y >> g.tile_log, by1 = g.primary_only ? by0 : (pc[q].i0y + g.w - 1) >> g.tile_log;
+    for (int by = by0; by <= by1; ++by)
+      for (int bx = bx0; bx <= bx1; ++bx) atomicAdd(&sh[by * g.TX + bx], 1u);
+  }
+  __syncthreads();
+  for (int b = t; b <= T; b += kBinThreads) sa.total[b] = (int)sh[b];
+  // a thread reads and then replaces the counts of its own bins only; entry T
+  // is read by all before any cursor is bumped
+  const int rejected = (int)sh[T];
+  __syncthreads();
+  if (t == 0) sh[T] = 0u;
+  bin_tables(T, sa.so, rejected, 0, bin_table_workgroups(T), [&](int b) { return (int)sh[b]; },
+             [&](int b, int rec0) { sh[b] = (unsigned)rec0; });
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < B; ++q)
+    if (t + q * kBinThreads < M) put_records(pc[q], g, t + q * kBinThreads, sh, T, a.recs, a.rej_end);
 }
 
 // Deterministic mode: the same counting sort with a stable scatter, so that
@@ -815,7 +1089,8 @@ struct __align__(16) MfmaRec {
 // Sub-batches of 256 records (one per thread), loaded one ahead: the LDS
 // footprint (about 24 KB at w = 7) and the registers leave room for six
 // workgroups per CU, which hide the load and LDS latencies.
-constexpr int kMfmaSB = kSpreadThreads;
+constexpr int kMfmaSB = kSpreadSubBatch;
+static_assert(kMfmaSB == kSpreadThreads, "one record per thread");
 
 // What an empty chunk (a bin with no records, which still writes its zero
 // tile) reads in place of its first record and that record's value: every
@@ -1195,6 +1470,41 @@ hipError_t launch_bin_scatter(const double* x, const double* y, int64_t M, BinGe
   if ((T + 1) * 4 <= kScatterCursorBytes)
     return launch_or_record<BinArgs, bin_scatter_body<true>, kBinThreads>(a, G, (T + 1) * 4, st);
   return launch_or_record<BinArgs, bin_scatter_body<false>, kBinThreads>(a, G, ((T + 1) / 2) * 4, st);
+}
+
+static BinScatterArgs scatter_args(const double* x, const double* y, int64_t M, const BinGeom& g, int ppw,
+                                   const int* off, int* total, const BinScanOut& so, BinRec* recs, int* rej_end) {
+  BinScatterArgs a{};
+  a.b.x = x;
+  a.b.y = y;
+  a.b.M = M;
+  a.b.g = g;
+  a.b.ppw = ppw;
+  a.b.off = off;
+  a.b.recs = recs;
+  a.b.rej_end = rej_end;
+  a.total = total;
+  a.so = so;
+  return a;
+}
+
+bool bin_scan_in_scatter(int T) { return (T + 1) * 4 <= kScatterCursorBytes; }
+
+hipError_t launch_bin_scatter_scan(const double* x, const double* y, int64_t M, BinGeom g, int ppw, int G,
+                                   const int* off, int* total, const BinScanOut& so, BinRec* recs, int* rej_end,
+                                   hipStream_t st) {
+  const int T = g.TX * g.TX;
+  if (!bin_scan_in_scatter(T) || G <= 0) return hipErrorInvalidValue;
+  return launch_or_record<BinScatterArgs, bin_scatter_scan_body, kBinThreads>(
+      scatter_args(x, y, M, g, ppw, off, total, so, recs, rej_end), G + bin_table_workgroups(T), (T + 1) * 4, st);
+}
+
+hipError_t launch_bin_small(const double* x, const double* y, int64_t M, BinGeom g, int* total, const BinScanOut& so,
+                            BinRec* recs, int* rej_end, hipStream_t st) {
+  const int T = g.TX * g.TX;
+  if (!bin_scan_in_scatter(T) || M < 1 || M > kBinSmall) return hipErrorInvalidValue;
+  return launch_or_record<BinScatterArgs, bin_small_body, kBinThreads>(
+      scatter_args(x, y, M, g, 0, nullptr, total, so, recs, rej_end), 1, (T + 1) * 4, st);
 }
 
 #define NUASM_DISPATCH_W(w, CALL)                                                   \

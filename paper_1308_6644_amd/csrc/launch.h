@@ -11,7 +11,7 @@ namespace nuasm {
 constexpr int kTile = 32;        // default fine cells per bin side (32 or 64)
 constexpr int kPad = 8;          // support margin: taps reach w/2 <= 8 cells past the window
 constexpr int kChunk = 2048;       // default max records per interpolation workgroup
-constexpr int kSpreadMinChunk = 256;  // one sub-batch of the matrix-core spreading
+constexpr int kSpreadSubBatch = 256;  // records per sub-batch of the matrix-core spreading
 constexpr int kSpreadChunk = 1792; // default max records per spreading workgroup
 // Spreading chunk sizes the kernel is instantiated for: whole sub-batches of
 // 448 records (w <= 8) or 256 (w > 8); `small` is about half the default.
@@ -121,7 +121,12 @@ struct BinArgs {
                            // most four per accepted point, never reach them)
 };
 
-// Outputs of the points outside the window (deferred range check) set to NaN.
+// Arguments of the scatters that scan the bin totals themselves.
+struct BinScatterArgs {
+  BinArgs b;
+  int* total;      // records per bin, then the points outside the window
+  BinScanOut so;
+};
 
 struct SpreadArgs {
   const BinRec* recs;
@@ -180,6 +185,7 @@ struct GridPts {
 hipError_t launch_fill_i32(int* p, int v, int64_t n, hipStream_t st);
 // counting sort of (point, bin) pairs: hist -> colscan -> scan -> scatter
 constexpr int kBinPointsMax = 65535;  // points per binning workgroup (16-bit LDS counters)
+constexpr int kBinSmall = 4096;        // most points binned by one workgroup
 constexpr int kBinPointsStable = 1024;  // the same in deterministic mode (stable scatter in LDS)
 // hist rows and offset rows have T + 1 entries (entry T: points outside the window)
 hipError_t launch_bin_hist(const double* x, const double* y, int64_t M, BinGeom g, int ppw, int G,
@@ -188,6 +194,13 @@ hipError_t launch_bin_hist(const double* x, const double* y, int64_t M, BinGeom 
 hipError_t launch_bin_colscan(const uint16_t* hist, int G, int T, int* off, int* total, const BinScanOut& so,
                               hipStream_t st);
 hipError_t launch_bin_scan(int T, const int* total, const BinScanOut& so, hipStream_t st);
+// Whether the bin count allows the scatters that scan the totals themselves.
+bool bin_scan_in_scatter(int T);
+hipError_t launch_bin_scatter_scan(const double* x, const double* y, int64_t M, BinGeom g, int ppw, int G,
+                                   const int* off, int* total, const BinScanOut& so, BinRec* recs, int* rej_end,
+                                   hipStream_t st);
+hipError_t launch_bin_small(const double* x, const double* y, int64_t M, BinGeom g, int* total, const BinScanOut& so,
+                            BinRec* recs, int* rej_end, hipStream_t st);
 hipError_t launch_bin_scatter(const double* x, const double* y, int64_t M, BinGeom g, int ppw, int G,
                               const int* off, const int* bin_base, BinRec* recs, int* rej_end, bool stable,
                               hipStream_t st);

@@ -663,9 +663,10 @@ void set_tile(nuasm_plan_s* pl, int tile) {
 // CUs idle while a few workgroups walk their sub-batches one after the other
 // (30011 clustered points on N' = 512, tol 1e-3: spreading 31 us with
 // 1792-record chunks, 7.5 with 256; interpolation 6.8 -> 3.9), so untuned
-// plans cut the bins finer: down to one sub-batch, but never to more than 2047
-// possible partial tiles (8 M / chunk), the bound that an allocation-free
-// execute has to meet.  Above 458 000 points that is the default size.
+// plans cut the bins finer: down to one sub-batch (two for up to 8192 points,
+// where the launch that sums split bins costs more, 3.4 us, than the second
+// sub-batch, 2.1), but never to more than 2047 possible partial tiles
+// (8 M / chunk), the bound that an allocation-free execute has to meet.  Above 458 000 points that is the default size.
 // Interpolation likewise, down to 512 records and at most 1024 chunks.  Plans
 // on a caller's workspace keep the default sizes their capacity was computed
 // from, and so do deterministic plans (their sums follow the chunks), the
@@ -679,7 +680,8 @@ void set_chunks(const nuasm_plan_s* pl, PointSet& q, int64_t M) {
   auto fit = [](int64_t need, int64_t lo, int64_t hi) {
     return (int)std::min(hi, std::max(lo, (need + 255) / 256 * 256));
   };
-  if (pl->sp_auto) q.sp_chunk = fit((8 * M + 2046) / 2047, kSpreadMinChunk, kSpreadChunk);
+  const int64_t lo = M <= 8192 ? 2 * kSpreadSubBatch : kSpreadSubBatch;
+  if (pl->sp_auto) q.sp_chunk = fit((8 * M + 2046) / 2047, lo, kSpreadChunk);
   if (pl->ip_auto) q.ip_chunk = fit((4 * M + kAutoChunks - 1) / kAutoChunks, 512, kChunk);
 }
 
@@ -805,7 +807,31 @@ nuasm_status bind_points(nuasm_plan_s* pl, PointSet& q, int64_t M, const double*
   if (s != NUASM_OK) return s;
   set_chunks(pl, q, M);
   hipStream_t st = pl->stream;
-  {
+  // With stage timing on, the binning keeps its four launches, each timed;
+  // the records and tables are the same.
+  const bool fused = M > 0 && !stable_bins(pl) && !pl->timing && bin_scan_in_scatter(pl->T);
+  if (fused) {
+    BinScanOut so{q.cursor, q.sp_chunks, q.sp_first, q.sp_n, q.multi, q.ip_chunks, q.nch,
+                  nullptr, nullptr, q.sp_chunk, q.ip_chunk};
+    if (M <= kBinSmall && pl->bin_ppw == 0) {
+      StageScope sc(pl, NUASM_STAGE_BIN_SCATTER);
+      HIP_TRY(launch_bin_small(x, y, M, pl->bgeom, q.counts, so, q.recs, rej_end(q), st), "launch bin_small");
+    } else {
+      int ppw = 0, G = 0;
+      bin_ranges(M, pl->bin_ppw, false, &ppw, &G);
+      {
+        StageScope sc(pl, NUASM_STAGE_BIN_HIST);
+        HIP_TRY(launch_bin_hist(x, y, M, pl->bgeom, ppw, G, q.hist, st), "launch bin_hist");
+      }
+      {
+        StageScope sc(pl, NUASM_STAGE_BIN_COLSCAN);
+        HIP_TRY(launch_bin_colscan(q.hist, G, pl->T, q.hoff, q.counts, so, st), "launch bin_colscan");
+      }
+      StageScope sc(pl, NUASM_STAGE_BIN_SCATTER);
+      HIP_TRY(launch_bin_scatter_scan(x, y, M, pl->bgeom, ppw, G, q.hoff, q.counts, so, q.recs, rej_end(q), st),
+              "launch bin_scatter");
+    }
+  } else {
     int ppw = 0, G = 0;
     bin_ranges(M, pl->bin_ppw, stable_bins(pl), &ppw, &G);
     if (M > 0) {
