@@ -178,7 +178,6 @@ struct GridPts {
   double tau0;
   int L;            // support side
   float two_over_w, beta_log2e;
-  int ty0, nrows;   // support rows the interpolation's x pass produces
 };
 
 // ---- launchers (return hipGetLastError() of the launch) -------------------
@@ -210,7 +209,7 @@ hipError_t launch_spread_mfma(int w, int tile, const SpreadArgs& a, int grid, hi
 hipError_t launch_spread_reduce(const SpreadReduceArgs& a, int grid, hipStream_t st);
 hipError_t launch_interp(int w, int tile, const InterpArgs& a, int grid, hipStream_t st);
 // separable interpolation at a grid: support (L x L) -> R (nrows x nx) -> out (ny x nx)
-hipError_t launch_grid_interp(int w, const float2* fine, float2* R, float2* out, const GridPts& p, hipStream_t st);
+hipError_t launch_grid_interp(int w, const float2* fine, float2* out, const GridPts& p, hipStream_t st);
 // separable spreading of grid values (ny x nx) -> S (ny x L) -> support (L x L)
 hipError_t launch_grid_spread(int w, const float2* vals, float2* S, float2* fine, const GridPts& p, hipStream_t st);
 

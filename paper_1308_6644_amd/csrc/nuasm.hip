@@ -908,21 +908,8 @@ nuasm_status bind_grid(nuasm_plan_s* pl, PointSet& q, int64_t nx, int64_t ny, do
   p.L = pl->geom.L;
   p.two_over_w = 2.0f / (float)pl->w;
   p.beta_log2e = pl->beta * 1.4426950408889634f;
-  // support rows the interpolation's taps reach, two rows of margin against
-  // the rounding of the host's and the device's tap positions
-  p.ty0 = 0;
-  p.nrows = 0;
-  if (nx > 0 && ny > 0) {
-    auto tap = [&](int64_t k) {
-      const double t = 2.0 * ((cy + (double)(k - ny / 2) * pitch) * p.inv_g) + p.tau0;
-      return (int)std::ceil(t - 0.5 * pl->w);
-    };
-    const int lo = std::max(0, tap(0) - 2);
-    const int hi = std::min(p.L, tap(ny - 1) + pl->w + 2);
-    p.ty0 = lo;
-    p.nrows = std::max(0, hi - lo);
-  }
-  const int64_t need = std::max<int64_t>((int64_t)p.nrows * nx, ny * (int64_t)p.L);
+  // rows spread along x, before the pass along y
+  const int64_t need = ny * (int64_t)p.L;
   if (need > q.gbuf_cap) {
     HIP_TRY(hipStreamSynchronize(pl->stream), "hipStreamSynchronize");
     if (q.gbuf) {
@@ -998,7 +985,7 @@ nuasm_status run_interp(nuasm_plan_s* pl, PointSet& q, const float2* grid, float
   if (q.M == 0) return NUASM_OK;
   StageScope sc(pl, NUASM_STAGE_INTERP);
   if (q.grid) {
-    HIP_TRY(launch_grid_interp(pl->w, grid, q.gbuf, out, q.gp, pl->stream), "launch grid_interp");
+    HIP_TRY(launch_grid_interp(pl->w, grid, out, q.gp, pl->stream), "launch grid_interp");
     return NUASM_OK;
   }
   InterpArgs ia{};
