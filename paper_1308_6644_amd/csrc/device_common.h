@@ -41,7 +41,7 @@ __device__ __forceinline__ float cos16(int m) {
 }
 __device__ __forceinline__ float sin16(int m) { return cos16(m < 4 ? 4 - m : m - 4) * (m <= 8 ? 1.f : -1.f); }
 
-// v * exp(DIR * 2 pi i m / 16), m compile-time after unrolling.
+// w * exp(DIR * 2 pi i m / 16), m compile-time after unrolling.
 template <int DIR>
 __device__ __forceinline__ float2 rot16(int m, float2 v) {
   if (m == 0) return v;
@@ -51,39 +51,104 @@ __device__ __forceinline__ float2 rot16(int m, float2 v) {
   return make_float2(c * v.x - s * v.y, c * v.y + s * v.x);
 }
 
-// In-register DFT of length R (R = 1, 2, 4, 8, 16), natural order in and out,
-// kernel exp(DIR * 2 pi i j k / R).  Radix-2 decimation in time.
-template <int R, int DIR>
-struct Dft {
-  static __device__ __forceinline__ void run(float2* x) {
-    float2 e[R / 2], o[R / 2];
-#pragma unroll
-    for (int i = 0; i < R / 2; ++i) {
-      e[i] = x[2 * i];
-      o[i] = x[2 * i + 1];
-    }
-    Dft<R / 2, DIR>::run(e);
-    Dft<R / 2, DIR>::run(o);
-#pragma unroll
-    for (int k = 0; k < R / 2; ++k) {
-      const float2 t = rot16<DIR>(k * (16 / R), o[k]);
-      x[k] = cadd(e[k], t);
-      x[k + R / 2] = csub(e[k], t);
-    }
-  }
-};
+// (a, b) -> (a + w b, a - w b): the sum in four fused multiply-adds, the
+// difference as 2 a less the sum in two.
+__device__ __forceinline__ void bfly(float2& a, float2& b, float2 w) {
+  const float2 r = make_float2(fmaf(-w.y, b.y, fmaf(w.x, b.x, a.x)), fmaf(w.y, b.x, fmaf(w.x, b.y, a.y)));
+  b = make_float2(fmaf(2.f, a.x, -r.x), fmaf(2.f, a.y, -r.y));
+  a = r;
+}
+// the same with w = 1, and with w = exp(DIR i pi / 2)
+__device__ __forceinline__ void bfly1(float2& a, float2& b) {
+  const float2 r = cadd(a, b);
+  b = csub(a, b);
+  a = r;
+}
 template <int DIR>
-struct Dft<2, DIR> {
-  static __device__ __forceinline__ void run(float2* x) {
-    const float2 a = x[0], b = x[1];
-    x[0] = cadd(a, b);
-    x[1] = csub(a, b);
+__device__ __forceinline__ void bfly_i(float2& a, float2& b) {
+  const float2 t = DIR < 0 ? make_float2(b.y, -b.x) : make_float2(-b.y, b.x);
+  const float2 r = cadd(a, t);
+  b = csub(a, t);
+  a = r;
+}
+
+// X[k] = sum_j x[j] w^j exp(DIR 2 pi i j k / R) in place, natural order, for
+// R = 2, 4, 8, by radix-2 decimation in time.  The twiddles of the pass are
+// taken inside the butterflies (w, w^2, w^4 and their rotations), six
+// operations each: 72 for R = 8 and 16 for the powers, where separate products
+// by w .. w^7 and a plain transform took 84 and 24.
+// PH: the pass has no twiddles of its own (w = exp(DIR 2 pi i PH / 16), PH = 0,
+// or 1 for the half-shifted first pass of radix 8); else w is given.
+template <int R, int DIR, int PH>
+__device__ __forceinline__ void dft_tw(float2 (&x)[R], float2 w) {
+  if constexpr (R == 2) {
+    bfly(x[0], x[1], w);
+  } else if constexpr (R == 4) {
+    const float2 w2 = cmul(w, w);
+    float2 e0 = x[0], e1 = x[2], o0 = x[1], o1 = x[3];
+    bfly(e0, e1, w2);
+    bfly(o0, o1, w2);
+    bfly(e0, o0, w);
+    bfly(e1, o1, rot16<DIR>(4, w));
+    x[0] = e0;
+    x[1] = e1;
+    x[2] = o0;
+    x[3] = o1;
+  } else {
+    static_assert(R == 8, "radix 2, 4 or 8");
+    // x[j]: even half (0, 4), (2, 6), odd half (1, 5), (3, 7)
+    const float2 one = make_float2(1.f, 0.f);
+    if constexpr (PH == 0) {
+      bfly1(x[0], x[4]);
+      bfly1(x[2], x[6]);
+      bfly1(x[1], x[5]);
+      bfly1(x[3], x[7]);
+      bfly1(x[0], x[2]);
+      bfly_i<DIR>(x[4], x[6]);
+      bfly1(x[1], x[3]);
+      bfly_i<DIR>(x[5], x[7]);
+      bfly1(x[0], x[1]);
+      bfly(x[4], x[5], rot16<DIR>(2, one));
+      bfly_i<DIR>(x[2], x[3]);
+      bfly(x[6], x[7], rot16<DIR>(6, one));
+    } else {
+      float2 w1 = w, w2, w4;
+      if constexpr (PH > 0) {
+        w1 = rot16<DIR>(PH, one);
+        w2 = rot16<DIR>(2 * PH, one);
+        bfly_i<DIR>(x[0], x[4]);
+        bfly_i<DIR>(x[2], x[6]);
+        bfly_i<DIR>(x[1], x[5]);
+        bfly_i<DIR>(x[3], x[7]);
+        static_assert(PH <= 1, "w^4 is a quarter turn");
+      } else {
+        w2 = cmul(w, w);
+        w4 = cmul(w2, w2);
+        bfly(x[0], x[4], w4);
+        bfly(x[2], x[6], w4);
+        bfly(x[1], x[5], w4);
+        bfly(x[3], x[7], w4);
+      }
+      const float2 w2i = rot16<DIR>(4, w2);
+      bfly(x[0], x[2], w2);
+      bfly(x[4], x[6], w2i);
+      bfly(x[1], x[3], w2);
+      bfly(x[5], x[7], w2i);
+      const float2 w1e = PH > 0 ? rot16<DIR>(2 + PH, one) : rot16<DIR>(2, w1);
+      bfly(x[0], x[1], w1);
+      bfly(x[4], x[5], w1e);
+      bfly(x[2], x[3], rot16<DIR>(4, w1));
+      bfly(x[6], x[7], rot16<DIR>(4, w1e));
+    }
+    // (x0, x4, x2, x6 | x1, x5, x3, x7) hold X0, X1, X2, X3 | X4, X5, X6, X7
+    const float2 t1 = x[4], t2 = x[2], t3 = x[6], t4 = x[1], t6 = x[3];
+    x[1] = t1;
+    x[2] = t2;
+    x[3] = t3;
+    x[4] = t4;
+    x[6] = t6;
   }
-};
-template <int DIR>
-struct Dft<1, DIR> {
-  static __device__ __forceinline__ void run(float2*) {}
-};
+}
 
 // LDS index with one pad slot per 16 complex elements: breaks the stride-16
 // bank pattern of the first Stockham pass.
@@ -115,162 +180,110 @@ __device__ __forceinline__ float2 tw2_get(const float2* __restrict__ t, int m) {
   return cmul(t[m >> 6], t[Tw2<LOGN>::HI + (m & 63)]);
 }
 
-// No-op input / output / hook for the passes below.
-struct NoIO {
-  __device__ __forceinline__ float2 operator()(int, int) const { return czero(); }
-  __device__ __forceinline__ void operator()(int, int, float2) const {}
-  __device__ __forceinline__ void operator()() const {}
-};
-
-// One radix-R Stockham pass over C interleaved transforms of length N held in
-// LDS (element t of transform c at pidx(t * C + c)), NT threads.  P is the
-// product of the radices of the earlier passes.  tw is the LDS two-level
-// twiddle table of length N (see Tw2).
+// Stockham transforms of C interleaved columns of length N = 2^LOGN whose data
+// live in registers between the passes' LDS exchanges.  Thread t < NA = C N / 8
+// of the workgroup's NT works on column c = t % C and owns the eight elements
+// i0 + m N / 8, m = 0 .. 7, i0 = t / C, before the transform and after it: a
+// caller loads its first pass's inputs straight into registers, uses the
+// outputs from registers, and chains two transforms of one length without an
+// exchange.  Passes of radix 8 with a 4 or 2 tail (two or four butterflies a
+// thread); the exchanges use element e of column c at pidx(e C + c).
 //
-// LOAD: the inputs come from ld(t, c) instead of LDS (first pass only, P = 1:
-// the kernel's global load feeds the butterflies directly, and no barrier is
-// needed before the LDS writes).  STORE: the outputs, in natural order at
-// this point (last pass, P R = N), go to st(t, c, v) instead of LDS, and
-// post() runs after them, before the closing barrier.
-template <int LOGN, int C, int NT, int DIR, int R, int P, bool LOAD, bool STORE, class Ld, class St, class Post>
-__device__ __forceinline__ void stockham_pass_io(float2* __restrict__ s, const float2* __restrict__ tw, int tid,
-                                                 const Ld& ld, const St& st, const Post& post) {
-  constexpr int N = 1 << LOGN;
-  constexpr int NR = N / R;
-  constexpr int NB = C * NR;
-  constexpr int PER = (NB + NT - 1) / NT;
-  constexpr int TWS = N / (P * R);
-  static_assert(!LOAD || P == 1, "only the first pass reads from the loader");
-  static_assert(!STORE || P * R == N, "only the last pass writes to the store");
-  float2 x[PER][R];
-  float2 w[PER][R];
+// HALF: the transform at the frequencies k + 1/2,
+//   X[k] = sum_t x[t] exp(DIR 2 pi i t (k + 1/2) / N).
+// Decimation in time carries the half through every pass (the sub-transforms
+// are half-shifted too), so it only changes the twiddles' index from k to
+// k + 1/2.  A transform of length 2 N whose input or output is half zero then
+// splits into two of length N, plain and half-shifted, one after the other in
+// half the LDS: with x zero outside N elements, X[2 q + p] is the transform of
+// x at q + p / 2.
+//
+// tw: LDS two-level table (Tw2) of length 2^TL, TL > LOGN for HALF.  The LDS
+// may still be in use by other threads when a transform begins (its first
+// pass waits before it writes); nothing is left in LDS at the end, but other
+// threads may still be reading.
+template <int LOGN, int C, int NT, int DIR, bool HALF, int TL, int P, int REM>
+__device__ __forceinline__ void reg_fft_pass(float2* __restrict__ s, const float2* __restrict__ tw, int tid,
+                                             float2 (&x)[8]) {
+  constexpr int N = 1 << LOGN, LR = REM >= 3 ? 3 : REM, R = 1 << LR, NR = N / R, PER = 8 / R;
+  constexpr int NA = C * N / 8, TWS = N / (P * R);
+  constexpr bool FIRST = P == 1, LAST = REM == LR;
+  static_assert(!FIRST || R == 8, "the first pass is radix 8");
+  static_assert(!FIRST || !LAST, "at least two passes");
+  static_assert(!HALF || TL > LOGN, "half-shifted twiddles need the table of twice the length");
+  static_assert(NA <= NT, "eight elements per thread");
+  const bool act = NA == NT || tid < NA;
+  const int c = tid % C, i0 = tid / C;
+  if (act) {
 #pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int b = tid + q * NT;
-    if (NB % NT == 0 || b < NB) {
-      const int c = b % C, i = b / C;
+    for (int q = 0; q < PER; ++q) {
+      const int i = i0 + q * (N / 8);
       const int k = i & (P - 1);
-      if constexpr (LOAD) {
+      float2 y[R];
+      if constexpr (FIRST) {
 #pragma unroll
-        for (int j = 0; j < R; ++j) x[q][j] = ld(i + j * NR, c);
-      } else if constexpr ((NR * C) % 16 == 0) {
-        // inputs NR * C elements apart: one padded address and constant
-        // offsets when the stride is a whole number of pad groups
-        const int p0 = pidx(i * C + c);
-#pragma unroll
-        for (int j = 0; j < R; ++j) x[q][j] = s[p0 + j * pidx(NR * C)];
+        for (int j = 0; j < R; ++j) y[j] = x[j];
+        dft_tw<R, DIR, HALF ? 1 : 0>(y, czero());
       } else {
+        if constexpr ((NR * C) % 16 == 0) {
+          // inputs NR * C elements apart: one padded address and constant
+          // offsets when the stride is a whole number of pad groups
+          const int p0 = pidx(i * C + c);
 #pragma unroll
-        for (int j = 0; j < R; ++j) x[q][j] = s[pidx((i + j * NR) * C + c)];
+          for (int j = 0; j < R; ++j) y[j] = s[p0 + j * pidx(NR * C)];
+        } else {
+#pragma unroll
+          for (int j = 0; j < R; ++j) y[j] = s[pidx((i + j * NR) * C + c)];
+        }
+        // exp(-2 pi i (k + HALF/2) TWS / N)
+        const int idx = TL > LOGN ? ((2 * k + (HALF ? 1 : 0)) * TWS) << (TL > LOGN ? TL - LOGN - 1 : 0) : k * TWS;
+        float2 w = tw2_get<TL>(tw, idx);
+        if (DIR > 0) w.y = -w.y;
+        dft_tw<R, DIR, -1>(y, w);
       }
-      if (P > 1) {
-        // w^j, w = exp(-2 pi i k TWS / N): one table lookup, then a power
-        // tree (each w^j a few products away from the table value)
-        w[q][1] = tw2_get<LOGN>(tw, k * TWS);
+      // register j * PER + q: in the last pass that is element i0 + m N / 8,
+      // m = q + j 8 / R
 #pragma unroll
-        for (int j = 2; j < R; ++j) {
-          const int hb = 1 << (31 - __builtin_clz(j));
-          w[q][j] = hb == j ? cmul(w[q][j / 2], w[q][j / 2]) : cmul(w[q][hb], w[q][j - hb]);
+      for (int j = 0; j < R; ++j) x[j * PER + q] = y[j];
+    }
+  }
+  if constexpr (!LAST) {
+    __syncthreads();
+    if (act) {
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        const int i = i0 + q * (N / 8);
+        const int k = i & (P - 1);
+        const int base = (i - k) * R + k;
+        if constexpr ((P * C) % 16 == 0) {
+          const int p0 = pidx(base * C + c);
+#pragma unroll
+          for (int j = 0; j < R; ++j) s[p0 + j * pidx(P * C)] = x[j * PER + q];
+        } else {
+#pragma unroll
+          for (int j = 0; j < R; ++j) s[pidx((base + j * P) * C + c)] = x[j * PER + q];
         }
       }
     }
+    __syncthreads();
+    reg_fft_pass<LOGN, C, NT, DIR, HALF, TL, P * R, REM - LR>(s, tw, tid, x);
   }
-  if constexpr (!LOAD) __syncthreads();
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int b = tid + q * NT;
-    if (NB % NT == 0 || b < NB) {
-      const int c = b % C, i = b / C;
-      const int k = i & (P - 1);
-      if (P > 1) {
-#pragma unroll
-        for (int j = 1; j < R; ++j) {
-          float2 t = w[q][j];
-          if (DIR > 0) t.y = -t.y;
-          x[q][j] = cmul(x[q][j], t);
-        }
-      }
-      Dft<R, DIR>::run(x[q]);
-      const int base = (i - k) * R + k;
-      if constexpr (STORE) {
-#pragma unroll
-        for (int j = 0; j < R; ++j) st(base + j * P, c, x[q][j]);
-      } else if constexpr ((P * C) % 16 == 0) {
-        const int p0 = pidx(base * C + c);
-#pragma unroll
-        for (int j = 0; j < R; ++j) s[p0 + j * pidx(P * C)] = x[q][j];
-      } else {
-#pragma unroll
-        for (int j = 0; j < R; ++j) s[pidx((base + j * P) * C + c)] = x[q][j];
-      }
-    }
-  }
-  if constexpr (STORE) post();
-  __syncthreads();
 }
 
-template <int LOGN, int C, int NT, int DIR, int R, int P>
-__device__ __forceinline__ void stockham_pass(float2* __restrict__ s, const float2* __restrict__ tw, int tid) {
-  stockham_pass_io<LOGN, C, NT, DIR, R, P, false, false>(s, tw, tid, NoIO{}, NoIO{}, NoIO{});
+template <int LOGN, int C, int NT, int DIR, bool HALF, int TL>
+__device__ __forceinline__ void reg_fft(float2* __restrict__ s, const float2* __restrict__ tw, int tid,
+                                        float2 (&x)[8]) {
+  reg_fft_pass<LOGN, C, NT, DIR, HALF, TL, 1, LOGN>(s, tw, tid, x);
 }
 
-// Radix-8 passes (a radix-4 or radix-2 tail) from P on, REM bits left; the
-// first one may read from the loader and the last one write to the store.
-template <int LOGN, int C, int NT, int DIR, int P, int REM, bool LOAD, bool STORE>
-struct FftPassesIO {
-  template <class Ld, class St, class Post>
-  static __device__ __forceinline__ void run(float2* s, const float2* tw, int tid, const Ld& ld, const St& st,
-                                             const Post& post) {
-    constexpr int LR = REM >= 3 ? 3 : REM;
-    constexpr int R = 1 << LR;
-    constexpr bool LAST = REM == LR;
-    stockham_pass_io<LOGN, C, NT, DIR, R, P, LOAD, STORE && LAST>(s, tw, tid, ld, st, post);
-    FftPassesIO<LOGN, C, NT, DIR, P * R, REM - LR, false, STORE>::run(s, tw, tid, ld, st, post);
-  }
-};
-template <int LOGN, int C, int NT, int DIR, int P, bool LOAD, bool STORE>
-struct FftPassesIO<LOGN, C, NT, DIR, P, 0, LOAD, STORE> {
-  template <class Ld, class St, class Post>
-  static __device__ __forceinline__ void run(float2*, const float2*, int, const Ld&, const St&, const Post&) {}
-};
-
-template <int LOGN, int C, int NT, int DIR, int P, int REM>
-struct FftPasses {
-  static __device__ __forceinline__ void run(float2* s, const float2* tw, int tid) {
-    FftPassesIO<LOGN, C, NT, DIR, P, REM, false, false>::run(s, tw, tid, NoIO{}, NoIO{}, NoIO{});
-  }
-};
-
-// FFT of C interleaved transforms of length 2^LOGN whose first pass reads
-// ld(t, c) (LOAD) and whose last pass hands the outputs, in natural order, to
-// st(t, c, v) and then runs post() (STORE); the passes in between use LDS as
-// fft_lds does.  Entered by all NT threads; with LOAD the twiddle table only
-// has to be in LDS by the end of the first pass (which has no twiddles), so
-// its staging needs no barrier of its own.  Ends with a barrier.
-template <int LOGN, int C, int NT, int DIR, bool LOAD, bool STORE, class Ld, class St, class Post>
-__device__ __forceinline__ void fft_io(float2* s, const float2* tw, int tid, const Ld& ld, const St& st,
-                                       const Post& post) {
-  FftPassesIO<LOGN, C, NT, DIR, 1, LOGN, LOAD, STORE>::run(s, tw, tid, ld, st, post);
+// Exchange between lanes of a pair (quad permutation 1, 0, 3, 2).
+__device__ __forceinline__ float pair_swap(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false));
 }
 
-// Unnormalised in-LDS FFT of C interleaved transforms of length 2^LOGN,
-// kernel exp(DIR * 2 pi i t k / N).  tw is the LDS two-level twiddle table of
-// that length.  Must be entered by all NT threads after the data and the
-// table are in LDS and a barrier; ends with a barrier.
-template <int LOGN, int C, int NT, int DIR>
-__device__ __forceinline__ void fft_lds(float2* s, const float2* tw) {
-  FftPasses<LOGN, C, NT, DIR, 1, LOGN>::run(s, tw, (int)threadIdx.x);
-}
-
-// The same transform with the thread index passed in.  A kernel that runs
-// two transforms of one length passes an opaque copy (opaque_tid) to the
-// second, so that the compiler recomputes its LDS addresses instead of
-// keeping the first transform's live across the code in between.
-template <int LOGN, int C, int NT, int DIR>
-__device__ __forceinline__ void fft_lds(float2* s, const float2* tw, int tid) {
-  FftPasses<LOGN, C, NT, DIR, 1, LOGN>::run(s, tw, tid);
-}
-
+// A copy of the thread index that the compiler cannot tie to the first: a
+// kernel with several transforms recomputes its LDS addresses in each instead
+// of keeping them all live.
 __device__ __forceinline__ int opaque_tid() {
   int t = (int)threadIdx.x;
   asm volatile("" : "+v"(t));

@@ -1,7 +1,7 @@
 // Grid passes of the two pipelines on gfx950: pruned row FFTs, the fused
 // column pass (FFT -> deconvolution x transfer function x Rect -> inverse FFT),
-// and the final row passes.  Every 1-D transform lives in LDS (Stockham,
-// radix 8 with a 4/2 tail); HBM is touched once per pass.
+// and the final row passes.  Data stay in registers between the LDS exchanges
+// of a transform (reg_fft); HBM is touched once per pass.
 //
 // Index conventions (centred, as in Eqs. 3, 6 and 9): a plane element [b][a]
 // of an N' x N' array holds n = (a - N'/2, b - N'/2); frequency k = a - N'/2.
@@ -9,8 +9,30 @@
 // or smaller when the band of Eq. 4 is narrow) and a fine grid of nf = 2 N''
 // cells per axis; the non-uniform window occupies fine cells
 // [N''/2, 3N''/2), and only the support rows/columns [s0, s0 + L),
-// L = N'' + 16, are ever stored.  Row passes over the fine grid are
-// instantiated at N''; the column passes go between N'' and N'.
+// L = N'' + 16, are ever stored.
+//
+// Half-length transforms.  Every transform of the fine grid has half its
+// cells (but for the 16 cells of margin) or half its modes empty, and so has
+// the transform of a zero-padded N x N plane: a transform of length 2 n is run
+// as two of length n, of the even and of the odd outputs (reg_fft, HALF), one
+// after the other in half the LDS, which leaves room for twice the rows or
+// columns in a workgroup.
+//
+// Intermediate layout.  Between a row pass and a column pass the array is
+// stored in strips of 2^cs columns, the column pass's own: element (row, col)
+// of an array of R rows at ((col >> cs) R + row) 2^cs + col mod 2^cs.  A column
+// workgroup then reads and writes one contiguous block, and a row workgroup of
+// C rows segments of C 2^cs elements, where row-major columns of one or two
+// elements had cost a 64-byte request each.  Before (full-length transforms in
+// LDS, row-major arrays, in-band strips alone launched) and now, us a launch:
+//   N' = 2048, half the columns in band  t1_cols  27.5  23.8   t1_rows      17.0  18.6
+//   N' = 2048, all columns               t2_cols  38.2  30.3   t2_rows_inv  18.9  19.3
+//                                        t3_cols  ~38   27.4   t1_rows_inv  16.0  14.1
+//   N' = 4096, 2522 columns              t1_cols 168.5  61.2   t1_rows      74.3  73.0
+//                                        t2_cols 134.5  64.1   t2_rows_inv  76.3  89.1
+//   N' = 8192, N'' = 2048, 2020 columns  t2_cols  91.5  48.8   t2_rows      75.4  79.3
+// The passes are bound by vector instruction issue (about 70 % at N' = 2048)
+// and the latency of their exchanges; the largest by cache requests.
 #include <algorithm>
 
 #include "group.h"
@@ -18,32 +40,81 @@
 
 namespace nuasm {
 
-// Row passes: C rows per workgroup, C * n = 4096 complex values in LDS.
-template <int LOGN>
+// Row passes: C rows per workgroup by transforms of length 2^LOG, eight
+// elements a thread; TL: log2 of the twiddle table's length.  ELEMS complex
+// values per workgroup (at least one row): small workgroups, which need fewer
+// waves at a barrier, suit the passes that write or read wide segments
+// (N'' = 2048, 2064 rows: t1_rows 20.0 us with two rows a workgroup, 19.1 with
+// one); the cropped pass, whose columns may come in strips of two, takes two
+// rows for 32-byte segments (N' = 4096: 30.8 us with one, 23 with two).
+constexpr int kRowElems = 2048, kCropRowElems = 4096;
+
+template <int LOG, int TL, int ELEMS = kRowElems>
 struct RowCfg {
-  static constexpr int N = 1 << LOGN;
-  static constexpr int C = N >= 4096 ? 1 : 4096 / N;
-  static constexpr int NB = C * N / 8;   // radix-8 butterflies per pass
-  static constexpr int NT = NB < 64 ? 64 : (NB > 1024 ? 1024 : NB);
-  static constexpr int DATA = lds_elems(C * N);  // complex elements of data
-  static constexpr int LDS = (DATA + Tw2<LOGN>::SIZE) * 8;
+  static constexpr int N = 1 << LOG;
+  static constexpr int C0 = ELEMS / N;
+  static constexpr int CMIN = N < 32 ? 512 / N : 1;  // at least a wave
+  static constexpr int C = C0 > 16 ? (CMIN > 16 ? CMIN : 16) : (C0 < 1 ? 1 : C0);
+  static constexpr int NT = C * N / 8;
+  static constexpr int DATA = lds_elems(C * N);
+  static constexpr int LDS = (DATA + Tw2<TL>::SIZE) * 8;
 };
 
-// Column passes: C adjacent columns per workgroup, C * nf = kColElems complex
-// values in LDS (one column when nf exceeds it), two workgroups per CU.
-constexpr int kColElems = 8192;  // complex values of fine length held per column workgroup
+// Column passes: C adjacent columns per workgroup, C * 2^LOG complex values in
+// LDS (LOG: the longest transform): workgroups of 512 threads, three or four
+// to a CU (N' = 2048, full band: t2_cols 38 us with 8192 values and 1024
+// threads, 31 with 4096, 41 with 2048).
+constexpr int kColElems = 4096;
 
-template <int LOGNF>
+constexpr int col_log(int log) {
+  int l = 0;
+  while (l < 4 && (kColElems >> (log + l + 1)) >= 1) ++l;
+  return l;
+}
+
+template <int LOG, int TL>
 struct ColCfg {
-  static constexpr int NF = 1 << LOGNF;
-  static constexpr int C0 = kColElems / NF;
-  static constexpr int C = C0 < 1 ? 1 : (C0 > 16 ? 16 : C0);
-  static constexpr int NB = C * NF / 8;
-  static constexpr int NT = NB < 64 ? 64 : (NB > 1024 ? 1024 : NB);
-  static constexpr int DATA = lds_elems(C * NF);
-  // twiddle tables for the fine length and for N' = NF / 2
-  static constexpr int LDS = (DATA + Tw2<LOGNF>::SIZE + Tw2<LOGNF - 1>::SIZE) * 8;
+  static constexpr int CS = col_log(LOG), C = 1 << CS;
+  static constexpr int NT = C * (1 << LOG) / 8;
+  static constexpr int DATA = lds_elems(C << LOG);
+  static constexpr int LDS = (DATA + Tw2<TL>::SIZE) * 8;
 };
+
+constexpr int imax(int a, int b) { return a > b ? a : b; }
+
+// Longest transform of the three column passes (their strip widths follow).
+constexpr int t1_cols_log(int lpf, int lp) { return imax(lpf, lp); }
+constexpr int t2_cols_log(int lpf, int lp, bool halfin) { return halfin && lpf < lp ? imax(lpf, lp - 1) : lp; }
+// Strip widths of the arrays a column pass reads (cs) and writes (cv), whole
+// multiples of its C columns.  A strip wider than C costs the column pass
+// partial requests and saves them in the row pass: four columns balance the
+// two, but for the array written by workgroups of one column, which take two
+// (N' = 4096: t2_cols 90 us with strips of four, 64 with two; t2_rows_inv 80
+// and 87).
+static void set_strips(GridGeom* g, int log) {
+  const int c = col_log(log);
+  g->cs = imax(2, c);
+  g->cv = c == 0 ? 1 : imax(2, c);
+}
+void set_t1_strips(GridGeom* g, int logNp) { set_strips(g, t1_cols_log(logNp, logNp)); }
+void set_t2_strips(GridGeom* g, int logNpf, int logNp) { set_strips(g, t2_cols_log(logNpf, logNp, g->Nin < g->Np)); }
+void set_t3_strips(GridGeom* g, int logNpf) { set_strips(g, logNpf); }
+
+// Element (row, col) of an array of `rows` rows stored in strips of 2^cs columns.
+__device__ __forceinline__ size_t strip_at(int rows, int cs, int row, int col) {
+  return (((size_t)(col >> cs) * rows + row) << cs) + (col & ((1 << cs) - 1));
+}
+
+// Columns col (even) and col + 1 of a row; cs is 0 only for the longest columns.
+__device__ __forceinline__ void strip_store2(float2* __restrict__ a, int rows, int cs, int row, int col, float2 v0,
+                                             float2 v1) {
+  if (cs > 0) {
+    *reinterpret_cast<float4*>(a + strip_at(rows, cs, row, col)) = make_float4(v0.x, v0.y, v1.x, v1.y);
+  } else {
+    a[strip_at(rows, cs, row, col)] = v0;
+    a[strip_at(rows, cs, row, col + 1)] = v1;
+  }
+}
 
 __device__ __forceinline__ bool in_band(int k, int lo, int hi) { return k >= lo && k <= hi; }
 
@@ -109,364 +180,531 @@ __device__ __forceinline__ float2 transfer_at(const Spectral& sp, int Np, int kx
   return h;
 }
 
+__device__ __forceinline__ float2 csel(bool ok, float2 v) { return ok ? v : czero(); }
+
+// The fine support along one axis as the input of the half-length transforms
+// of length N = N'': element u = i0 + m N/8 gathers the cells u and u + N of
+// the fine axis that lie in the support.  at(i) reads support cell i.  main[m]
+// is cell u + N for m < 4 and u for m >= 4 (always inside the support), and
+// edge[m] the other one, inside it for 2 kPad of the u only.
+template <int N, class At>
+__device__ __forceinline__ void load_support(int i0, const At& at, float2 (&main)[8], float2 (&edge)[8]) {
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    const int u = i0 + m * (N / 8);
+    edge[m] = czero();
+    if (m < 4) {
+      main[m] = at(u + N / 2 + kPad);
+      if ((m + 1) * (N / 8) > N / 2 - kPad && u >= N / 2 - kPad) edge[m] = at(u - N / 2 + kPad);
+    } else {
+      main[m] = at(u - N / 2 + kPad);
+      if (m * (N / 8) < N / 2 + kPad && u < N / 2 + kPad) edge[m] = at(u + N / 2 + kPad);
+    }
+  }
+}
+
+// Input of the half-length transform of parity p: cells u + N enter with
+// (-1)^p.
+__device__ __forceinline__ void fold_support(int p, const float2 (&main)[8], const float2 (&edge)[8], float2 (&x)[8]) {
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    const float2 hi = m < 4 ? main[m] : edge[m], lo = m < 4 ? edge[m] : main[m];
+    x[m] = p ? csub(lo, hi) : cadd(lo, hi);
+  }
+}
+
+// Whether element m of eight (i0 + m N/8, taken as signed, [-N/2, N/2)) can lie
+// in [-K/2, K/2).
+constexpr bool mode_kept(int m, int N, int K) { return (m < 4 ? m : 7 - m) * (N / 8) < K / 2; }
+
 // ----------------------------------------------------------------- type 1
-// Fine support rows -> nf-point FFT along x -> keep k_x in K, times 1/psihat.
-// T[i][a] = sum_l G[i][l] exp(-2 pi i k_x (s0 + l) / nf) / psihat(k_x).
-template <int LOGNP>
-__device__ __forceinline__ void t1_rows_body(const RowArgs& a, int bid, int) {
+// Fine support rows -> nf-point FFT along x -> keep k_x in K'', times 1/psihat.
+// T(i, k_x) = sum_l G[i][l] exp(-2 pi i k_x (s0 + l) / nf) / psihat(k_x).
+template <int LOG>
+__device__ __forceinline__ void t1_rows_body(const RowArgs& a, int bid, int nbid) {
   const float2* __restrict__ fine = a.in;
   float2* __restrict__ T = a.out;
   const GridGeom& g = a.g;
   const float* __restrict__ dinv = a.dinv;
-  constexpr int LOGN = LOGNP + 1, NF = 1 << LOGN, NP = 1 << LOGNP;
-  using Cfg = RowCfg<LOGN>;
+  constexpr int N = 1 << LOG, TL = LOG + 1;
+  using Cfg = RowCfg<LOG, TL>;
   constexpr int C = Cfg::C, NT = Cfg::NT;
   extern __shared__ float2 s[];
   float2* tw = s + Cfg::DATA;
-  load_tw2<LOGN, NT>(tw, tw_for(a.tw, LOGN));
-  const int r0 = bid * C;
-  const int L = g.L, s0 = g.s0;
-  // the first pass reads the support rows (zero outside), the last one
-  // writes the kept k_x; loads are clamped and selected, never branched over
-  const auto ld = [&](int t, int c) -> float2 {
-    const int row = r0 + c, i = t - s0;
-    const float2 v = fine[(size_t)min(row, L - 1) * L + min(max(i, 0), L - 1)];
-    return (row < L && i >= 0 && i < L) ? v : czero();
-  };
-  const auto st = [&](int t, int c, float2 v) {
-    const int row = r0 + c, kx = t < NF / 2 ? t : t - NF;
-    if (row < L && kx >= -NP / 2 && kx < NP / 2 && in_band(kx, g.kxlo, g.kxhi))
-      T[(size_t)row * NP + kx + NP / 2] = cscale(v, dinv[kx + NP / 2]);
-  };
-  fft_io<LOGN, C, NT, -1, true, true>(s, tw, (int)threadIdx.x, ld, st, NoIO{});
+  const int tid = (int)threadIdx.x, i0 = tid / C;
+  const int L = g.L, row = xcd_remap(bid, nbid) * C + tid % C;
+  const float2* src = fine + (size_t)min(row, L - 1) * L;
+  float2 x[8], h[8], main[8], edge[8];
+  load_support<N>(i0, [&](int i) { return src[i]; }, main, edge);
+  load_tw2<TL, NT>(tw, tw_for(a.tw, TL));
+  fold_support(0, main, edge, h);
+  reg_fft<LOG, C, NT, -1, false, TL>(s, tw, tid, h);
+  fold_support(1, main, edge, x);
+  reg_fft<LOG, C, NT, -1, true, TL>(s, tw, opaque_tid(), x);
+  if (row >= L) return;
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    if (m >= 2 && m < 6) continue;  // outside K''
+    const int q = i0 + m * (N / 8), kx = 2 * (m < 4 ? q : q - N), ax = kx + N / 2;
+    if (kx + 1 >= g.kxlo && kx <= g.kxhi)
+      strip_store2(T, L, g.cs, row, ax, cscale(h[m], dinv[ax]), cscale(x[m], dinv[ax + 1]));
+  }
 }
 
-// Column passes that change length: a forward FFT of one length and an
-// inverse FFT of another over the same columns; C adjacent columns sized by
-// the longer of the two.
-template <int LOGA, int LOGB>
-struct Col2Cfg {
-  static constexpr int LMAX = LOGA > LOGB ? LOGA : LOGB;
-  static constexpr int NMAX = 1 << LMAX;
-  static constexpr int C0 = kColElems / NMAX;
-  static constexpr int C = C0 < 1 ? 1 : (C0 > 16 ? 16 : C0);
-  static constexpr int NB = C * NMAX / 8;
-  static constexpr int NT = NB < 64 ? 64 : (NB > 1024 ? 1024 : NB);
-  static constexpr int DATA = lds_elems(C * NMAX);
-  static constexpr int LDS = (DATA + Tw2<LOGA>::SIZE + Tw2<LOGB>::SIZE) * 8;
-};
-
 // Columns of T -> nf-point FFT along y -> keep k_y in the spectral grid K''
-// (N'' = NPF modes, a superset of the band of Eq. 4; N'' = N' unless the band
+// (N'' modes, a superset of the band of Eq. 4; N'' = N' unless the band
 // is narrow) -> times H(k) Rect(k) / psihat(k_y) / N'^2 -> embedded in K ->
-// N'-point inverse FFT along y.  T holds the columns k_x + N''/2; V is
-// written with N' columns, k_x + N'/2.  The (-1)^k factors of the centred
-// fine grid and of the centred inverse DFT cancel (N'/2 is even); the
-// remaining output sign (-1)^n_y is applied here.
-template <int LOGNPF, int LOGNP>
+// N'-point inverse FFT along y.  T holds the columns k_x + N''/2; V has N'
+// columns, k_x + N'/2, and N' rows (the central N when cropping).  The (-1)^k
+// factors of the centred fine grid and of the centred inverse DFT cancel
+// (N'/2 is even); the remaining output sign (-1)^n_y is applied here.
+template <int LPF, int LP>
 __device__ __forceinline__ void t1_cols_body(const ColArgs& a, int bid, int nbid) {
-  const float2* __restrict__ T = a.in;
-  float2* __restrict__ V = a.out;
   const GridGeom& g = a.g;
   const Spectral& sp = a.sp;
-  const float2* __restrict__ twall = a.tw;
-  constexpr int LOGN = LOGNPF + 1, NF = 1 << LOGN, NPF = 1 << LOGNPF, NP = 1 << LOGNP;
-  using Cfg = Col2Cfg<LOGN, LOGNP>;
-  constexpr int C = Cfg::C, NT = Cfg::NT;
+  constexpr int N = 1 << LPF, NP = 1 << LP, TL = imax(LPF + 1, LP);
+  using Cfg = ColCfg<t1_cols_log(LPF, LP), TL>;
+  constexpr int C = Cfg::C, NT = Cfg::NT, NA = C * N / 8;
   extern __shared__ float2 s[];
-  const int a0 = (band_strip0(g, NPF, C) + xcd_remap(bid, nbid)) * C;
-  const int kx0 = a0 - NPF / 2;
-  float2* twf = s + Cfg::DATA;
-  float2* twp = twf + Tw2<LOGN>::SIZE;
-  load_tw2<LOGN, NT>(twf, tw_for(twall, LOGN));
-  load_tw2<LOGNP, NT>(twp, tw_for(twall, LOGNP));
-  const int L = g.L, s0 = g.s0;
-  // forward transform: the first pass reads the support rows of T, the last
-  // one applies H Rect / psihat / N'^2 to the modes of K'' and writes them,
-  // embedded in K, as the inverse transform's input (the rest of K zeroed)
-  const auto ld = [&](int t, int c) -> float2 {
-    const int i = t - s0;
-    const float2 v = T[(size_t)min(max(i, 0), L - 1) * NPF + a0 + c];
-    return (i >= 0 && i < L && in_band(kx0 + c, g.kxlo, g.kxhi)) ? v : czero();
+  float2* tw = s + Cfg::DATA;
+  const int a0 = (band_strip0(g, N, C) + xcd_remap(bid, nbid)) * C;
+  const int kx0 = a0 - N / 2;
+  const int tid = (int)threadIdx.x, c = tid % C, i0 = tid / C, kx = kx0 + c;
+  const int L = g.L;
+  const bool inx = in_band(kx, g.kxlo, g.kxhi);
+  float2 x[8], h[8], main[8], edge[8];
+  if (NA == NT || tid < NA) {
+    const float2* src = a.in + strip_at(L, g.cs, 0, a0) + c;
+    load_support<N>(i0, [&](int i) { return csel(inx, src[i << g.cs]); }, main, edge);
+  }
+  load_tw2<TL, NT>(tw, tw_for(a.tw, TL));
+  // H Rect / psihat / N'^2 at mode 2 q + p of element m
+  auto spectral = [&](int m, int p, float2 v) -> float2 {
+    const int q = i0 + m * (N / 8), ky = 2 * (m < 4 ? q : q - N) + p;
+    if (!inx || !in_band(ky, g.kylo, g.kyhi)) return czero();
+    return cscale(cmul(v, transfer_at(sp, NP, kx, ky)), sp.dinv[ky + N / 2] * sp.scale);
   };
-  const auto mid = [&](int t, int c, float2 v) {
-    const int ky = t < NF / 2 ? t : t - NF, kx = kx0 + c;
-    if (ky < -NPF / 2 || ky >= NPF / 2) return;  // outside K''
-    float2 x = czero();
-    if (in_band(kx, g.kxlo, g.kxhi) && in_band(ky, g.kylo, g.kyhi)) {
-      x = cmul(v, transfer_at(sp, NP, kx, ky));
-      x = cscale(x, sp.dinv[ky + NPF / 2] * sp.scale);
+  fold_support(0, main, edge, h);
+  reg_fft<LPF, C, NT, -1, false, TL>(s, tw, tid, h);
+  if (NA == NT || tid < NA) {
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+      if (m < 2 || m >= 6) h[m] = spectral(m, 0, h[m]);
+  }
+  fold_support(1, main, edge, x);
+  reg_fft<LPF, C, NT, -1, true, TL>(s, tw, opaque_tid(), x);
+  __syncthreads();
+  if (NA == NT || tid < NA) {
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      if (m >= 2 && m < 6) continue;  // outside K''
+      const int q = i0 + m * (N / 8), ay = 2 * (m < 4 ? q : q - N) + NP / 2;
+      s[pidx(ay * C + c)] = h[m];
+      s[pidx((ay + 1) * C + c)] = spectral(m, 1, x[m]);
     }
-    s[pidx((ky + NP / 2) * C + c)] = x;
-  };
-  const auto gap = [&]() {
-    if constexpr (NPF < NP) {
-      // K outside K'': [0, (N' - N'')/2) and [(N' + N'')/2, N')
-      constexpr int H = (NP - NPF) / 2;
-      for (int e = threadIdx.x; e < 2 * H * C; e += NT) {
-        const int u = e / C, c = e % C;
-        const int ay = u < H ? u : u + NPF;
-        s[pidx(ay * C + c)] = czero();
-      }
+  }
+  if constexpr (N < NP) {
+    // K outside K'': [0, (N' - N'')/2) and [(N' + N'')/2, N')
+    constexpr int H = (NP - N) / 2;
+    for (int e = tid; e < 2 * H * C; e += NT) {
+      const int u = e / C, ay = u < H ? u : u + N;
+      s[pidx(ay * C + c)] = czero();
     }
-  };
-  fft_io<LOGN, C, NT, -1, true, true>(s, twf, (int)threadIdx.x, ld, mid, gap);
-  // inverse transform along y; the last pass writes V with the (-1)^n_y sign
-  const auto st = [&](int by, int c, float2 x) {
-    const int kx = kx0 + c;
-    if (in_band(kx, g.kxlo, g.kxhi)) {
-      if (by & 1) x = make_float2(-x.x, -x.y);
-      V[(size_t)by * NP + kx + NP / 2] = x;
-    }
-  };
-  fft_io<LOGNP, C, NT, +1, false, true>(s, twp, opaque_tid(), NoIO{}, st, NoIO{});
+  }
+  __syncthreads();
+  const int t2 = opaque_tid(), j0 = t2 / C, c2 = t2 % C;
+#pragma unroll
+  for (int m = 0; m < 8; ++m) x[m] = s[pidx((j0 + m * (NP / 8)) * C + c2)];
+  reg_fft<LP, C, NT, +1, false, TL>(s, tw, t2, x);
+  // V: this strip's columns, with the (-1)^n_y sign
+  const int nrows = g.crop ? NP / 2 : NP, row0 = g.crop ? NP / 4 : 0;
+  float2* dst = a.out + strip_at(nrows, g.cv, 0, a0 - N / 2 + NP / 2) + c2;
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    const int by = j0 + m * (NP / 8), r = by - row0;
+    if (r >= 0 && r < nrows) dst[r << g.cv] = (by & 1) ? make_float2(-x[m].x, -x[m].y) : x[m];
+  }
 }
 
 // Rows of V -> N'-point inverse FFT along x -> times (-1)^n_x -> plane
-// (N' x N', or the central N x N when cropping).
-template <int LOGNP>
-__device__ __forceinline__ void t1_rows_inv_body(const RowArgs& a, int bid, int) {
+// (N' x N'), or, when cropping, the central N x N: the outputs
+// [N'/4, 3N'/4) of each parity from half-length transforms.
+template <int LP>
+__device__ __forceinline__ void t1_rows_inv_body(const RowArgs& a, int bid, int nbid) {
   const float2* __restrict__ V = a.in;
   float2* __restrict__ out = a.out;
   const GridGeom& g = a.g;
-  constexpr int NP = 1 << LOGNP;
-  using Cfg = RowCfg<LOGNP>;
+  constexpr int N = 1 << LP;
+  using Cfg = RowCfg<LP, LP>;
   constexpr int C = Cfg::C, NT = Cfg::NT;
   extern __shared__ float2 s[];
   float2* tw = s + Cfg::DATA;
-  load_tw2<LOGNP, NT>(tw, tw_for(a.tw, LOGNP));
-  const int nrows = g.crop ? g.N : NP;
-  const int rowoff = g.crop ? g.N / 2 : 0;
-  const int r0 = bid * C;
-  const auto ld = [&](int a, int c) -> float2 {
-    const int r = r0 + c, kx = a - NP / 2;
-    const float2 v = V[(size_t)(min(r, nrows - 1) + rowoff) * NP + a];
-    return (r < nrows && in_band(kx, g.kxlo, g.kxhi)) ? v : czero();
-  };
-  const auto st = [&](int bx, int c, float2 x) {
-    const int r = r0 + c;
-    if (r >= nrows) return;
-    if (bx & 1) x = make_float2(-x.x, -x.y);
-    if (g.crop) {
-      const int ox = bx - g.N / 2;
-      if (ox >= 0 && ox < g.N) out[(size_t)r * g.N + ox] = x;
+  const int tid = (int)threadIdx.x, i0 = tid / C;
+  const int row = xcd_remap(bid, nbid) * C + tid % C, rowc = min(row, N - 1);
+  float2 x[8];
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    const int ax = i0 + m * (N / 8);
+    x[m] = csel(in_band(ax - N / 2, g.kxlo, g.kxhi), V[strip_at(N, g.cv, rowc, ax)]);
+  }
+  load_tw2<LP, NT>(tw, tw_for(a.tw, LP));
+  reg_fft<LP, C, NT, +1, false, LP>(s, tw, tid, x);
+  if (row >= N) return;
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    const int bx = i0 + m * (N / 8);
+    out[(size_t)row * N + bx] = (bx & 1) ? make_float2(-x[m].x, -x[m].y) : x[m];
+  }
+}
+
+template <int LP>
+__device__ __forceinline__ void t1_rows_inv_crop_body(const RowArgs& a, int bid, int nbid) {
+  const float2* __restrict__ V = a.in;
+  float2* __restrict__ out = a.out;
+  const GridGeom& g = a.g;
+  constexpr int LOG = LP - 1, N = 1 << LOG, TL = LP;
+  using Cfg = RowCfg<LOG, TL, kCropRowElems>;
+  constexpr int C = Cfg::C, NT = Cfg::NT;
+  extern __shared__ float2 s[];
+  float2* tw = s + Cfg::DATA;
+  const int tid = (int)threadIdx.x, i0 = tid / C;
+  const int row = xcd_remap(bid, nbid) * C + tid % C, rowc = min(row, N - 1);
+  float2 h[8], x[8];
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    // modes u and u + N of the N'-point transform
+    const int u = i0 + m * (N / 8);
+    const float2 lo = csel(in_band(u - N, g.kxlo, g.kxhi), V[strip_at(N, g.cv, rowc, u)]);
+    const float2 hi = csel(in_band(u, g.kxlo, g.kxhi), V[strip_at(N, g.cv, rowc, u + N)]);
+    h[m] = cadd(lo, hi);
+    x[m] = csub(lo, hi);
+  }
+  load_tw2<TL, NT>(tw, tw_for(a.tw, TL));
+  reg_fft<LOG, C, NT, +1, false, TL>(s, tw, tid, h);
+  reg_fft<LOG, C, NT, +1, true, TL>(s, tw, opaque_tid(), x);
+  if (row >= N) return;
+  // outputs 2 q (sign +) and 2 q + 1 (sign -) of the central N columns; the
+  // caller's plane may be aligned to one element only
+  float2* dst = out + (size_t)row * N;
+  const bool wide = ((uintptr_t)out & 15) == 0;
+#pragma unroll
+  for (int m = 2; m < 6; ++m) {
+    const int ox = 2 * (i0 + m * (N / 8)) - N / 2;
+    if (wide) {
+      *reinterpret_cast<float4*>(dst + ox) = make_float4(h[m].x, h[m].y, -x[m].x, -x[m].y);
     } else {
-      out[(size_t)r * NP + bx] = x;
+      dst[ox] = h[m];
+      dst[ox + 1] = make_float2(-x[m].x, -x[m].y);
     }
-  };
-  fft_io<LOGNP, C, NT, +1, true, true>(s, tw, (int)threadIdx.x, ld, st, NoIO{});
+  }
 }
 
 // ----------------------------------------------------------------- type 2
 // Rows of the Nin x Nin plane, zero-padded circularly to N' -> FFT along x ->
-// times (-1)^k_x / psihat(k_x), centred output T[row][k_x + N'/2].
-template <int LOGNP>
-__device__ __forceinline__ void t2_rows_body(const RowArgs& a, int bid, int) {
+// times (-1)^k_x / psihat(k_x), T(row, k_x + N'/2).  HALFIN: Nin = N, by
+// half-length transforms of the even and odd modes; else Nin = N'.
+template <int LP, bool HALFIN>
+__device__ __forceinline__ void t2_rows_body(const RowArgs& a, int bid, int nbid) {
   const float2* __restrict__ u1 = a.in;
   float2* __restrict__ T = a.out;
   const GridGeom& g = a.g;
   const float* __restrict__ dinv = a.dinv;
-  constexpr int NP = 1 << LOGNP;
-  using Cfg = RowCfg<LOGNP>;
+  constexpr int LOG = HALFIN ? LP - 1 : LP, N = 1 << LOG, NP = 1 << LP, TL = LP;
+  using Cfg = RowCfg<LOG, TL>;
   constexpr int C = Cfg::C, NT = Cfg::NT;
   extern __shared__ float2 s[];
   float2* tw = s + Cfg::DATA;
-  load_tw2<LOGNP, NT>(tw, tw_for(a.tw, LOGNP));
-  const int Nin = g.Nin;
-  const int r0 = bid * C;
-  const auto ld = [&](int t, int c) -> float2 {
-    const int r = r0 + c, mx = t < NP / 2 ? t : t - NP;
-    const int mc = min(max(mx, -Nin / 2), Nin / 2 - 1);
-    const float2 v = u1[(size_t)min(r, Nin - 1) * Nin + mc + Nin / 2];
-    return (r < Nin && mx >= -Nin / 2 && mx < Nin / 2) ? v : czero();
-  };
-  const auto st = [&](int t, int c, float2 v) {
-    const int r = r0 + c, kx = t < NP / 2 ? t : t - NP;
-    if (r < Nin && in_band(kx, g.kxlo, g.kxhi)) {
-      float2 x = cscale(v, dinv[kx + NP / 2]);
-      if (kx & 1) x = make_float2(-x.x, -x.y);
-      T[(size_t)r * NP + kx + NP / 2] = x;
+  const int tid = (int)threadIdx.x, i0 = tid / C;
+  const int row = xcd_remap(bid, nbid) * C + tid % C;
+  const float2* src = u1 + (size_t)min(row, N - 1) * N;
+  float2 x[8];
+  // element u: sample u of the row's upper half, or u - N of its lower half
+#pragma unroll
+  for (int m = 0; m < 8; ++m) x[m] = src[i0 + m * (N / 8) + (m < 4 ? N / 2 : -N / 2)];
+  load_tw2<TL, NT>(tw, tw_for(a.tw, TL));
+  if constexpr (HALFIN) {
+    float2 h[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      h[m] = x[m];
+      if (m >= 4) x[m] = make_float2(-x[m].x, -x[m].y);
     }
-  };
-  fft_io<LOGNP, C, NT, -1, true, true>(s, tw, (int)threadIdx.x, ld, st, NoIO{});
+    reg_fft<LOG, C, NT, -1, false, TL>(s, tw, tid, h);
+    reg_fft<LOG, C, NT, -1, true, TL>(s, tw, opaque_tid(), x);
+    if (row >= N) return;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int q = i0 + m * (N / 8), kx = 2 * (m < 4 ? q : q - N), ax = kx + NP / 2;
+      if (kx + 1 >= g.kxlo && kx <= g.kxhi)
+        strip_store2(T, N, g.cs, row, ax, cscale(h[m], dinv[ax]), cscale(x[m], -dinv[ax + 1]));
+    }
+  } else {
+    reg_fft<LOG, C, NT, -1, false, TL>(s, tw, tid, x);
+    if (row >= N) return;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int t = i0 + m * (N / 8), kx = m < 4 ? t : t - N, ax = kx + N / 2;
+      if (in_band(kx, g.kxlo, g.kxhi)) T[strip_at(N, g.cs, row, ax)] = cscale(x[m], (kx & 1) ? -dinv[ax] : dinv[ax]);
+    }
+  }
+}
+
+// The modes k of element m (signed, [-N''/2, N''/2)) as the input of the
+// half-length inverse transform of parity p: negative modes enter with (-1)^p.
+__device__ __forceinline__ void fold_modes(const float2 (&v)[8], float2 (&x)[8]) {
+#pragma unroll
+  for (int m = 0; m < 8; ++m) x[m] = m < 4 ? v[m] : make_float2(-v[m].x, -v[m].y);
+}
+
+// Support rows 2 q - s0 and 2 q + 1 - s0 of a column strip (outputs 2 q and
+// 2 q + 1 of the nf-point inverse transform): lanes of a pair of columns
+// exchange halves, so that each stores two columns of one row.
+template <int N, int C>
+__device__ __forceinline__ void store_support_rows(float2* __restrict__ strip, int L, int cs, int tid, const float2 (&h)[8],
+                                                   const float2 (&x)[8]) {
+  const int c = tid % C, i0 = tid / C;
+  constexpr int s0 = N / 2 - kPad;
+#pragma unroll
+  for (int m = 1; m < 7; ++m) {
+    const int i = 2 * (i0 + m * (N / 8)) - s0;
+    if constexpr (C > 1) {
+      const bool odd = c & 1;
+      const float2 give = odd ? h[m] : x[m];
+      const float2 got = make_float2(pair_swap(give.x), pair_swap(give.y));
+      const float4 v = odd ? make_float4(got.x, got.y, x[m].x, x[m].y) : make_float4(h[m].x, h[m].y, got.x, got.y);
+      if (i >= 0 && i < L)
+        *reinterpret_cast<float4*>(strip + ((i + (odd ? 1 : 0)) << cs) + (c & ~1)) = v;
+    } else if (i >= 0 && i < L) {
+      strip[i << cs] = h[m];
+      strip[(i + 1) << cs] = x[m];
+    }
+  }
 }
 
 // Columns of T (Nin rows, N' columns k_x + N'/2) -> N'-point FFT along y ->
-// the modes k_y of the spectral grid K'' (N'' = NPF, a superset of the band
-// of Eq. 4) times H(k) Rect(k) (-1)^k_y / psihat(k_y) / N'^2, embedded in the
-// nf-point spectrum (nf = 2 N'', the gap zero) -> inverse nf-point FFT along
-// y -> the support rows [s0, s0 + L), written with N'' columns k_x + N''/2.
-template <int LOGNPF, int LOGNP>
+// the modes k_y of the spectral grid K'' (N'' modes, a superset of the band
+// of Eq. 4) times H(k) Rect(k) (-1)^k_y / psihat(k_y) / N'^2 -> inverse
+// nf-point FFT along y (nf = 2 N'') -> the support rows [s0, s0 + L), N''
+// columns k_x + N''/2.  HALFIN: Nin = N.  With a narrow band (N'' < N') the
+// forward transform of a half-empty column runs by half-length transforms and
+// its modes reach the inverse one through LDS; otherwise it runs at full
+// length, which leaves every mode in the register where the inverse
+// transforms want it.
+template <int LPF, int LP, bool HALFIN>
 __device__ __forceinline__ void t2_cols_body(const ColArgs& a, int bid, int nbid) {
-  const float2* __restrict__ T = a.in;
-  float2* __restrict__ V = a.out;
   const GridGeom& g = a.g;
   const Spectral& sp = a.sp;
-  const float2* __restrict__ twall = a.tw;
-  constexpr int LOGN = LOGNPF + 1, NF = 1 << LOGN, NPF = 1 << LOGNPF, NP = 1 << LOGNP;
-  using Cfg = Col2Cfg<LOGNP, LOGN>;
-  constexpr int C = Cfg::C, NT = Cfg::NT;
+  constexpr int N = 1 << LPF, NP = 1 << LP, TL = imax(LPF + 1, LP);
+  constexpr bool SPLIT = HALFIN && LPF < LP;
+  using Cfg = ColCfg<t2_cols_log(LPF, LP, HALFIN), TL>;
+  constexpr int C = Cfg::C, NT = Cfg::NT, NA = C * N / 8;
   extern __shared__ float2 s[];
+  float2* tw = s + Cfg::DATA;
   const int a0 = (band_strip0(g, NP, C) + xcd_remap(bid, nbid)) * C;
   const int kx0 = a0 - NP / 2;
-  float2* twp = s + Cfg::DATA;
-  float2* twf = twp + Tw2<LOGNP>::SIZE;
-  load_tw2<LOGNP, NT>(twp, tw_for(twall, LOGNP));
-  load_tw2<LOGN, NT>(twf, tw_for(twall, LOGN));
-  const int Nin = g.Nin;
-  // forward transform along y: the first pass reads the Nin rows of T
-  // (circularly zero-padded), the last one applies H Rect (-1)^k_y / psihat /
-  // N'^2 to the modes of K'' and writes them into the nf-point spectrum of the
-  // inverse transform, whose gap it zeroes
-  const auto ld = [&](int t, int c) -> float2 {
-    const int my = t < NP / 2 ? t : t - NP;
-    const int mc = min(max(my, -Nin / 2), Nin / 2 - 1);
-    const float2 v = T[(size_t)(mc + Nin / 2) * NP + a0 + c];
-    return (my >= -Nin / 2 && my < Nin / 2 && in_band(kx0 + c, g.kxlo, g.kxhi)) ? v : czero();
+  if (kx0 < -N / 2 || kx0 >= N / 2) return;  // outside K'' (a band empty along y): no column of V
+  const int tid = (int)threadIdx.x, c = tid % C, i0 = tid / C, kx = kx0 + c;
+  const bool inx = in_band(kx, g.kxlo, g.kxhi);
+  const int Nin = HALFIN ? NP / 2 : NP;
+  const float2* src = a.in + strip_at(Nin, g.cs, 0, a0) + c;
+  auto row = [&](int r) { return csel(inx, src[r << g.cs]); };
+  auto spectral = [&](int ky, float2 v) -> float2 {
+    if (!inx || !in_band(ky, g.kylo, g.kyhi)) return czero();
+    return cscale(cmul(v, transfer_at(sp, NP, kx, ky)),
+                  sp.dinv[ky + N / 2] * sp.scale * ((ky & 1) ? -1.0f : 1.0f));
   };
-  const auto mid = [&](int t, int c, float2 v) {
-    const int ky = t < NP / 2 ? t : t - NP, kx = kx0 + c;
-    if (ky < -NPF / 2 || ky >= NPF / 2) return;  // outside K''
-    float2 x = czero();
-    if (in_band(kx, g.kxlo, g.kxhi) && in_band(ky, g.kylo, g.kyhi)) {
-      x = cmul(v, transfer_at(sp, NP, kx, ky));
-      x = cscale(x, sp.dinv[ky + NPF / 2] * sp.scale * ((ky & 1) ? -1.0f : 1.0f));
+  float2 v[8];  // modes i0 + m N''/8 of the inverse transforms
+  if constexpr (SPLIT) {
+    constexpr int LH = LP - 1, H = 1 << LH, NF = C * H / 8;
+    float2 h[8], x[8];
+    const bool act = NF == NT || tid < NF;
+    if (act) {
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        h[m] = row(i0 + m * (H / 8) + (m < 4 ? H / 2 : -H / 2));
+        x[m] = m < 4 ? h[m] : make_float2(-h[m].x, -h[m].y);
+      }
     }
-    s[pidx(((ky + NF) & (NF - 1)) * C + c)] = x;
-  };
-  const auto gap = [&]() {
-    // the gap between the two halves of K'' inside the nf-point spectrum
-    for (int e = threadIdx.x; e < C * (NF - NPF); e += NT) {
-      const int t = NPF / 2 + e / C, c = e % C;
-      s[pidx(t * C + c)] = czero();
+    load_tw2<TL, NT>(tw, tw_for(a.tw, TL));
+    reg_fft<LH, C, NT, -1, false, TL>(s, tw, tid, h);
+    reg_fft<LH, C, NT, -1, true, TL>(s, tw, opaque_tid(), x);
+    __syncthreads();
+    if (act) {
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        // even mode ky, odd mode ky + 1; K'' keeps q in [-N''/4, N''/4)
+        if (!mode_kept(m, H, N / 2)) continue;
+        const int q = i0 + m * (H / 8), ky = 2 * (m < 4 ? q : q - H);
+        if (ky < -N / 2 || ky >= N / 2) continue;
+        s[pidx((ky & (N - 1)) * C + c)] = spectral(ky, h[m]);
+        s[pidx(((ky + 1) & (N - 1)) * C + c)] = spectral(ky + 1, x[m]);
+      }
     }
-  };
-  fft_io<LOGNP, C, NT, -1, true, true>(s, twp, (int)threadIdx.x, ld, mid, gap);
-  // inverse nf-point transform; the last pass keeps the support rows
-  const int L = g.L, s0 = g.s0;
-  const auto st = [&](int t, int c, float2 v) {
-    const int i = t - s0, kx = kx0 + c;
-    if (i >= 0 && i < L && in_band(kx, g.kxlo, g.kxhi)) V[(size_t)i * NPF + kx + NPF / 2] = v;
-  };
-  fft_io<LOGN, C, NT, +1, false, true>(s, twf, opaque_tid(), NoIO{}, st, NoIO{});
+    __syncthreads();
+  } else {
+    float2 x[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int t = i0 + m * (NP / 8);
+      if (HALFIN)
+        x[m] = m < 2 ? row(t + NP / 4) : m >= 6 ? row(t - NP + NP / 4) : czero();
+      else
+        x[m] = row(m < 4 ? t + NP / 2 : t - NP / 2);
+    }
+    load_tw2<TL, NT>(tw, tw_for(a.tw, TL));
+    reg_fft<LP, C, NT, -1, false, TL>(s, tw, tid, x);
+    if constexpr (LPF < LP) __syncthreads();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int t = i0 + m * (NP / 8), ky = m < 4 ? t : t - NP;
+      if constexpr (LPF == LP) {
+        v[m] = spectral(ky, x[m]);
+      } else if (mode_kept(m, NP, N)) {
+        if (ky >= -N / 2 && ky < N / 2) s[pidx((ky & (N - 1)) * C + c)] = spectral(ky, x[m]);
+      }
+    }
+    if constexpr (LPF < LP) __syncthreads();
+  }
+  if constexpr (LPF < LP) {
+    if (NA == NT || tid < NA) {
+#pragma unroll
+      for (int m = 0; m < 8; ++m) v[m] = s[pidx((i0 + m * (N / 8)) * C + c)];
+    }
+  }
+  float2 x[8];
+  fold_modes(v, x);
+  const int t2 = opaque_tid();
+  reg_fft<LPF, C, NT, +1, false, TL>(s, tw, t2, v);
+  reg_fft<LPF, C, NT, +1, true, TL>(s, tw, t2, x);
+  if (NA == NT || t2 < NA) store_support_rows<N, C>(a.out + strip_at(g.L, g.cv, 0, kx0 + N / 2), g.L, g.cv, t2, v, x);
 }
 
 // Support rows of V -> embed k_x into nf -> inverse nf-point FFT along x ->
 // keep support columns: the fine grid the interpolation reads.
-template <int LOGNP>
-__device__ __forceinline__ void t2_rows_inv_body(const RowArgs& a, int bid, int) {
+template <int LOG>
+__device__ __forceinline__ void t2_rows_inv_body(const RowArgs& a, int bid, int nbid) {
   const float2* __restrict__ V = a.in;
   float2* __restrict__ fine = a.out;
   const GridGeom& g = a.g;
-  constexpr int LOGN = LOGNP + 1, NF = 1 << LOGN, NP = 1 << LOGNP;
-  using Cfg = RowCfg<LOGN>;
+  constexpr int N = 1 << LOG, TL = LOG + 1;
+  using Cfg = RowCfg<LOG, TL>;
   constexpr int C = Cfg::C, NT = Cfg::NT;
   extern __shared__ float2 s[];
   float2* tw = s + Cfg::DATA;
-  load_tw2<LOGN, NT>(tw, tw_for(a.tw, LOGN));
-  const int L = g.L, s0 = g.s0;
-  const int r0 = bid * C;
-  // the first pass reads the row's k_x into the nf-point spectrum (the gap
-  // zero), the last one keeps the support columns
-  const auto ld = [&](int t, int c) -> float2 {
-    const int r = r0 + c;
-    const bool lo = t < NP / 2, hi = t >= NF - NP / 2;
-    const int kx = lo ? t : hi ? t - NF : 0;
-    const float2 v = V[(size_t)min(r, L - 1) * NP + kx + NP / 2];
-    return (r < L && (lo || hi) && in_band(kx, g.kxlo, g.kxhi)) ? v : czero();
-  };
-  const auto st = [&](int t, int c, float2 v) {
-    const int r = r0 + c, i = t - s0;
-    if (r < L && i >= 0 && i < L) fine[(size_t)r * L + i] = v;
-  };
-  fft_io<LOGN, C, NT, +1, true, true>(s, tw, (int)threadIdx.x, ld, st, NoIO{});
+  const int tid = (int)threadIdx.x, i0 = tid / C;
+  const int L = g.L, row = xcd_remap(bid, nbid) * C + tid % C, rowc = min(row, L - 1);
+  float2 h[8], x[8];
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    const int ax = i0 + m * (N / 8) + (m < 4 ? N / 2 : -N / 2);
+    h[m] = csel(in_band(ax - N / 2, g.kxlo, g.kxhi), V[strip_at(L, g.cv, rowc, ax)]);
+  }
+  load_tw2<TL, NT>(tw, tw_for(a.tw, TL));
+  fold_modes(h, x);
+  reg_fft<LOG, C, NT, +1, false, TL>(s, tw, tid, h);
+  reg_fft<LOG, C, NT, +1, true, TL>(s, tw, opaque_tid(), x);
+  if (row >= L) return;
+  // outputs 2 q and 2 q + 1 that lie in the support
+  float2* dst = fine + (size_t)row * L;
+#pragma unroll
+  for (int m = 1; m < 7; ++m) {
+    const int i = 2 * (i0 + m * (N / 8)) - (N / 2 - kPad);
+    if (i >= 0 && i < L) *reinterpret_cast<float4*>(dst + i) = make_float4(h[m].x, h[m].y, x[m].x, x[m].y);
+  }
 }
 
 // ----------------------------------------------------------------- type 3
 // Column pass of NU-ASM_3 / NU-FRE_3 (non-uniform source and destination),
 // between the type-1 row pass over the source's fine support and the type-2
 // inverse row pass over the destination's: columns of T -> nf-point FFT along
-// y -> keep k_y in K (the gap outside K zeroed) -> times H(k) Rect(k) N'^-2
+// y -> keep k_y in K'' -> times H(k) Rect(k) N'^-2
 // and the three deconvolutions not applied elsewhere, 1/psihat(k_y) of the
 // spreading, 1/psihat(k_y) and 1/psihat(k_x) of the interpolation -> inverse
 // nf-point FFT along y -> the support rows [s0, s0 + L).  Both grids are fine
 // grids, so the (-1)^k factors of the window offset cancel between the
-// forward and the inverse transform on each axis.  Every element is scaled
-// in place by its own thread: one LDS buffer, no register staging.
-template <int LOGNF>
-struct T3Cfg {
-  using Col = ColCfg<LOGNF>;
-  static constexpr int C = Col::C, NT = Col::NT, DATA = Col::DATA;
-  static constexpr int LDS = (DATA + Tw2<LOGNF>::SIZE) * 8;
-  // waves per SIMD when two workgroups share a CU (LDS permitting): the
-  // register budget is held to what that occupancy allows
-  static constexpr int WAVES = LDS <= 80 * 1024 ? 2 * NT / 256 : NT / 256;
-};
-
-template <int LOGNP>
-__global__ void __launch_bounds__(T3Cfg<LOGNP + 1>::NT)
-__attribute__((amdgpu_waves_per_eu(T3Cfg<LOGNP + 1>::WAVES)))
+// forward and the inverse transform on each axis.
+template <int LPF>
+__global__ void __launch_bounds__((ColCfg<LPF, LPF + 1>::NT))
 k_t3_cols(const float2* __restrict__ T, float2* __restrict__ V, GridGeom g, Spectral sp,
           const float2* __restrict__ twall) {
-  constexpr int LOGN = LOGNP + 1, NF = 1 << LOGN, NP = 1 << LOGNP;
-  using Cfg = T3Cfg<LOGN>;
-  constexpr int C = Cfg::C, NT = Cfg::NT;
-  extern __shared__ float2 s[];
-  const int a0 = (band_strip0(g, NP, C) + xcd_remap((int)blockIdx.x, (int)gridDim.x)) * C;
-  const int kx0 = a0 - NP / 2;
-  float2* twf = s + Cfg::DATA;
-  load_tw2<LOGN, NT>(twf, tw_for(twall, LOGN));
-  const int L = g.L, s0 = g.s0;
-  // forward transform: the first pass reads the support rows of T, the last
-  // one scales every mode in place (zero outside K and the band)
-  const auto ld = [&](int t, int c) -> float2 {
-    const int i = t - s0;
-    const float2 v = T[(size_t)min(max(i, 0), L - 1) * NP + a0 + c];
-    return (i >= 0 && i < L && in_band(kx0 + c, g.kxlo, g.kxhi)) ? v : czero();
-  };
-  const auto mid = [&](int t, int c, float2 v) {
-    const int ky = t < NF / 2 ? t : t - NF;
-    const int kx = kx0 + c;
-    float2 x = czero();
-    if (ky >= -NP / 2 && ky < NP / 2 && in_band(kx, g.kxlo, g.kxhi) && in_band(ky, g.kylo, g.kyhi)) {
-      const float2 h = transfer_at(sp, g.Np, kx, ky);
-      const float dy = sp.dinv[ky + NP / 2];
-      x = cmul(v, h);
-      x = cscale(x, dy * dy * sp.dinv[kx + NP / 2] * sp.scale);
-    }
-    s[pidx(t * C + c)] = x;
-  };
-  fft_io<LOGN, C, NT, -1, true, true>(s, twf, (int)threadIdx.x, ld, mid, NoIO{});
-  // inverse transform; the last pass keeps the support rows
-  const auto st = [&](int t, int c, float2 v) {
-    const int i = t - s0;
-    if (i >= 0 && i < L && in_band(kx0 + c, g.kxlo, g.kxhi)) V[(size_t)i * NP + a0 + c] = v;
-  };
-  fft_io<LOGN, C, NT, +1, false, true>(s, twf, opaque_tid(), NoIO{}, st, NoIO{});
-}
-
-// ----------------------------------------------------------- test kernels
-template <int LOGN, int DIR>
-__global__ void __launch_bounds__(RowCfg<LOGN>::NT)
-k_fft_rows(const float2* __restrict__ in, float2* __restrict__ out, int64_t batch,
-           const float2* __restrict__ twall) {
-  constexpr int N = 1 << LOGN;
-  using Cfg = RowCfg<LOGN>;
+  constexpr int N = 1 << LPF, TL = LPF + 1;
+  using Cfg = ColCfg<LPF, TL>;
   constexpr int C = Cfg::C, NT = Cfg::NT;
   extern __shared__ float2 s[];
   float2* tw = s + Cfg::DATA;
+  const int a0 = (band_strip0(g, N, C) + xcd_remap((int)blockIdx.x, (int)gridDim.x)) * C;
+  const int tid = (int)threadIdx.x, c = tid % C, i0 = tid / C, kx = a0 - N / 2 + c;
+  const int L = g.L;
+  const bool inx = in_band(kx, g.kxlo, g.kxhi);
+  float2 x[8], h[8], main[8], edge[8];
+  const float2* src = T + strip_at(L, g.cs, 0, a0) + c;
+  load_support<N>(i0, [&](int i) { return csel(inx, src[i << g.cs]); }, main, edge);
+  load_tw2<TL, NT>(tw, tw_for(twall, TL));
+  const float dx = inx ? sp.dinv[kx + N / 2] * sp.scale : 0.f;
+  auto spectral = [&](int m, int p, float2 v) -> float2 {
+    const int q = i0 + m * (N / 8), ky = 2 * (m < 4 ? q : q - N) + p;
+    if (!inx || !in_band(ky, g.kylo, g.kyhi)) return czero();
+    const float dy = sp.dinv[ky + N / 2];
+    return cscale(cmul(v, transfer_at(sp, g.Np, kx, ky)), dy * dy * dx);
+  };
+  fold_support(0, main, edge, h);
+  reg_fft<LPF, C, NT, -1, false, TL>(s, tw, tid, h);
+#pragma unroll
+  for (int m = 0; m < 8; ++m)
+    if (m < 2 || m >= 6) h[m] = spectral(m, 0, h[m]);
+  fold_support(1, main, edge, x);
+  reg_fft<LPF, C, NT, -1, true, TL>(s, tw, opaque_tid(), x);
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    if (m >= 2 && m < 6) continue;  // outside K''
+    const int q = i0 + m * (N / 8), u = (2 * q) & (N - 1);  // mode 2 q mod N''
+    s[pidx(u * C + c)] = h[m];
+    s[pidx((u + 1) * C + c)] = spectral(m, 1, x[m]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < 8; ++m) h[m] = s[pidx((i0 + m * (N / 8)) * C + c)];
+  fold_modes(h, x);
+  const int t2 = opaque_tid();
+  reg_fft<LPF, C, NT, +1, false, TL>(s, tw, t2, h);
+  reg_fft<LPF, C, NT, +1, true, TL>(s, tw, t2, x);
+  store_support_rows<N, C>(V + strip_at(L, g.cv, 0, a0), L, g.cv, t2, h, x);
+}
+
+// ----------------------------------------------------------- test kernels
+// Batched 1-D transforms of length 2^LOGN by the half-length transforms of the
+// even and odd outputs.
+template <int LOGN, int DIR>
+__global__ void __launch_bounds__((RowCfg<LOGN - 1, LOGN>::NT))
+k_fft_rows(const float2* __restrict__ in, float2* __restrict__ out, int64_t batch,
+           const float2* __restrict__ twall) {
+  constexpr int LOG = LOGN - 1, N = 1 << LOG;
+  using Cfg = RowCfg<LOG, LOGN>;
+  constexpr int C = Cfg::C, NT = Cfg::NT;
+  extern __shared__ float2 s[];
+  float2* tw = s + Cfg::DATA;
+  const int tid = (int)threadIdx.x, i0 = tid / C;
+  const int64_t r = (int64_t)blockIdx.x * C + tid % C;
+  const float2* src = in + (r < batch ? r : batch - 1) * 2 * N;
+  float2 h[8], x[8];
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    const int u = i0 + m * (N / 8);
+    const float2 lo = src[u], hi = src[u + N];
+    h[m] = cadd(lo, hi);
+    x[m] = csub(lo, hi);
+  }
   load_tw2<LOGN, NT>(tw, tw_for(twall, LOGN));
-  const int64_t r0 = (int64_t)blockIdx.x * C;
-  const auto ld = [&](int t, int c) -> float2 {
-    const int64_t r = r0 + c;
-    const float2 v = in[(r < batch ? r : batch - 1) * N + t];
-    return r < batch ? v : czero();
-  };
-  const auto st = [&](int t, int c, float2 v) {
-    const int64_t r = r0 + c;
-    if (r < batch) out[r * N + t] = v;
-  };
-  fft_io<LOGN, C, NT, DIR, true, true>(s, tw, (int)threadIdx.x, ld, st, NoIO{});
+  reg_fft<LOG, C, NT, DIR, false, LOGN>(s, tw, tid, h);
+  reg_fft<LOG, C, NT, DIR, true, LOGN>(s, tw, opaque_tid(), x);
+  if (r >= batch) return;
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    const int q = i0 + m * (N / 8);
+    out[r * 2 * N + 2 * q] = h[m];
+    out[r * 2 * N + 2 * q + 1] = x[m];
+  }
 }
 
 __global__ void k_transfer_table(GridGeom g, Spectral sp, float2* __restrict__ out) {
@@ -545,11 +783,11 @@ static hipError_t set_lds(K kernel, int bytes) {
 hipError_t launch_t1_rows(int logNp, const float2* fine, float2* T, GridGeom g, const float* dinv,
                           const float2* tw, hipStream_t st) {
   const RowArgs a{fine, T, g, dinv, tw};
-#define CALL(LP)                                                                              \
-  {                                                                                           \
-    using Cfg = RowCfg<LP + 1>;                                                               \
-    return launch_or_record<RowArgs, t1_rows_body<LP>, Cfg::NT>(a, (g.L + Cfg::C - 1) / Cfg::C, \
-                                                                Cfg::LDS, st);                \
+#define CALL(LP)                                                                                 \
+  {                                                                                              \
+    using Cfg = RowCfg<LP, LP + 1>;                                                              \
+    return launch_or_record<RowArgs, t1_rows_body<LP>, Cfg::NT>(a, (g.L + Cfg::C - 1) / Cfg::C,  \
+                                                                Cfg::LDS, st);                   \
   }
   NUASM_DISPATCH_NP(logNp, CALL)
 #undef CALL
@@ -561,17 +799,24 @@ hipError_t launch_t1_rows(int logNp, const float2* fine, float2* T, GridGeom g, 
 template <int LPF, int LP>
 static hipError_t t1_cols_at(const float2* T, float2* V, const GridGeom& g, const Spectral& sp, const float2* tw,
                              hipStream_t st) {
-  using Cfg = Col2Cfg<LPF + 1, LP>;
+  using Cfg = ColCfg<t1_cols_log(LPF, LP), imax(LPF + 1, LP)>;
   return launch_or_record<ColArgs, t1_cols_body<LPF, LP>, Cfg::NT>(
       ColArgs{T, V, g, sp, tw}, band_strips(g, 1 << LPF, Cfg::C), Cfg::LDS, st);
+}
+
+template <int LPF, int LP, bool HALFIN>
+static hipError_t t2_cols_in(const float2* T, float2* V, const GridGeom& g, const Spectral& sp, const float2* tw,
+                             hipStream_t st) {
+  using Cfg = ColCfg<t2_cols_log(LPF, LP, HALFIN), imax(LPF + 1, LP)>;
+  return launch_or_record<ColArgs, t2_cols_body<LPF, LP, HALFIN>, Cfg::NT>(
+      ColArgs{T, V, g, sp, tw}, band_strips(g, 1 << LP, Cfg::C), Cfg::LDS, st);
 }
 
 template <int LPF, int LP>
 static hipError_t t2_cols_at(const float2* T, float2* V, const GridGeom& g, const Spectral& sp, const float2* tw,
                              hipStream_t st) {
-  using Cfg = Col2Cfg<LP, LPF + 1>;
-  return launch_or_record<ColArgs, t2_cols_body<LPF, LP>, Cfg::NT>(
-      ColArgs{T, V, g, sp, tw}, band_strips(g, 1 << LP, Cfg::C), Cfg::LDS, st);
+  return g.Nin < g.Np ? t2_cols_in<LPF, LP, true>(T, V, g, sp, tw, st)
+                      : t2_cols_in<LPF, LP, false>(T, V, g, sp, tw, st);
 }
 
 template <int LP, bool T1>
@@ -603,12 +848,15 @@ hipError_t launch_t1_cols(int logNpf, int logNp, const float2* T, float2* V, Gri
 hipError_t launch_t1_rows_inv(int logNp, const float2* V, float2* out, GridGeom g, const float2* tw,
                               hipStream_t st) {
   const RowArgs a{V, out, g, nullptr, tw};
-#define CALL(LP)                                                                                      \
-  {                                                                                                   \
-    using Cfg = RowCfg<LP>;                                                                           \
-    const int nrows = g.crop ? g.N : (1 << LP);                                                       \
-    return launch_or_record<RowArgs, t1_rows_inv_body<LP>, Cfg::NT>(a, (nrows + Cfg::C - 1) / Cfg::C, \
-                                                                    Cfg::LDS, st);                    \
+#define CALL(LP)                                                                                             \
+  {                                                                                                          \
+    using Full = RowCfg<LP, LP>;                                                                             \
+    using Crop = RowCfg<LP - 1, LP, kCropRowElems>;                                                                         \
+    constexpr int NP = 1 << LP;                                                                              \
+    if (g.crop)                                                                                              \
+      return launch_or_record<RowArgs, t1_rows_inv_crop_body<LP>, Crop::NT>(                                 \
+          a, (NP / 2 + Crop::C - 1) / Crop::C, Crop::LDS, st);                                               \
+    return launch_or_record<RowArgs, t1_rows_inv_body<LP>, Full::NT>(a, (NP + Full::C - 1) / Full::C, Full::LDS, st); \
   }
   NUASM_DISPATCH_NP(logNp, CALL)
 #undef CALL
@@ -618,11 +866,15 @@ hipError_t launch_t1_rows_inv(int logNp, const float2* V, float2* out, GridGeom 
 hipError_t launch_t2_rows(int logNp, const float2* u1, float2* T, GridGeom g, const float* dinv,
                           const float2* tw, hipStream_t st) {
   const RowArgs a{u1, T, g, dinv, tw};
-#define CALL(LP)                                                                                \
-  {                                                                                             \
-    using Cfg = RowCfg<LP>;                                                                     \
-    return launch_or_record<RowArgs, t2_rows_body<LP>, Cfg::NT>(a, (g.Nin + Cfg::C - 1) / Cfg::C, \
-                                                                Cfg::LDS, st);                  \
+#define CALL(LP)                                                                                                 \
+  {                                                                                                              \
+    using Full = RowCfg<LP, LP>;                                                                                 \
+    using Half = RowCfg<LP - 1, LP>;                                                                             \
+    if (g.Nin < g.Np)                                                                                            \
+      return launch_or_record<RowArgs, t2_rows_body<LP, true>, Half::NT>(a, (g.Nin + Half::C - 1) / Half::C,     \
+                                                                         Half::LDS, st);                         \
+    return launch_or_record<RowArgs, t2_rows_body<LP, false>, Full::NT>(a, (g.Nin + Full::C - 1) / Full::C,      \
+                                                                        Full::LDS, st);                          \
   }
   NUASM_DISPATCH_NP(logNp, CALL)
 #undef CALL
@@ -641,11 +893,11 @@ hipError_t launch_t2_cols(int logNpf, int logNp, const float2* T, float2* V, Gri
 hipError_t launch_t2_rows_inv(int logNp, const float2* V, float2* fine, GridGeom g, const float2* tw,
                               hipStream_t st) {
   const RowArgs a{V, fine, g, nullptr, tw};
-#define CALL(LP)                                                                                   \
-  {                                                                                                \
-    using Cfg = RowCfg<LP + 1>;                                                                    \
+#define CALL(LP)                                                                                    \
+  {                                                                                                 \
+    using Cfg = RowCfg<LP, LP + 1>;                                                                 \
     return launch_or_record<RowArgs, t2_rows_inv_body<LP>, Cfg::NT>(a, (g.L + Cfg::C - 1) / Cfg::C, \
-                                                                    Cfg::LDS, st);                 \
+                                                                    Cfg::LDS, st);                  \
   }
   NUASM_DISPATCH_NP(logNp, CALL)
 #undef CALL
@@ -656,7 +908,7 @@ hipError_t launch_t3_cols(int logNp, const float2* T, float2* V, GridGeom g, Spe
                           const float2* tw, hipStream_t st) {
 #define CALL(LP)                                                                         \
   {                                                                                      \
-    using Cfg = T3Cfg<LP + 1>;                                                           \
+    using Cfg = ColCfg<LP, LP + 1>;                                                      \
     hipError_t e = set_lds(k_t3_cols<LP>, Cfg::LDS);                                     \
     if (e != hipSuccess) return e;                                                       \
     const int grid = band_strips(g, 1 << LP, Cfg::C);                                    \
@@ -672,7 +924,7 @@ hipError_t launch_fft_rows(int logn, int64_t batch, int sign, const float2* in, 
                            const float2* tw, hipStream_t st) {
 #define CALL2(LN, D)                                                                     \
   {                                                                                      \
-    using Cfg = RowCfg<LN>;                                                              \
+    using Cfg = RowCfg<LN - 1, LN>;                                                      \
     hipError_t e = set_lds(k_fft_rows<LN, D>, Cfg::LDS);                                 \
     if (e != hipSuccess) return e;                                                       \
     const int64_t grid = (batch + Cfg::C - 1) / Cfg::C;                                  \

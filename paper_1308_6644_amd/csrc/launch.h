@@ -30,6 +30,7 @@ struct GridGeom {
   int kylo, kyhi;
   int Nin;         // side of the uniform input of the type-2 pipeline (N, or N' for the type-1 adjoint)
   int crop;        // type-1 pipeline writes only the central N x N
+  int cs, cv;      // log2 of the strip widths of the column pass's input and output
 };
 
 // Everything the fused spectral kernels need to form D(kx) D(ky) H(k) R(k).
@@ -213,6 +214,10 @@ hipError_t launch_grid_interp(int w, const float2* fine, float2* out, const Grid
 // separable spreading of grid values (ny x nx) -> S (ny x L) -> support (L x L)
 hipError_t launch_grid_spread(int w, const float2* vals, float2* S, float2* fine, const GridPts& p, hipStream_t st);
 
+// the strip widths (GridGeom::cs, cv) of a pipeline's intermediate arrays
+void set_t1_strips(GridGeom* g, int logNp);
+void set_t2_strips(GridGeom* g, int logNpf, int logNp);  // after Nin
+void set_t3_strips(GridGeom* g, int logNpf);
 // type-1 pipeline: fine support (L x L) -> rows -> fused columns -> rows -> plane
 // (row passes over the fine grid take log2 N'', the column pass both sizes)
 hipError_t launch_t1_rows(int logNp, const float2* fine, float2* T, GridGeom g, const float* dinv,

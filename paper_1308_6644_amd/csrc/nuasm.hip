@@ -1015,6 +1015,7 @@ nuasm_status run_type1_pipeline(nuasm_plan_s* pl, PointSet& q, const float2* val
   if (s != NUASM_OK) return s;
   GridGeom g = pl->geom;
   g.crop = crop ? 1 : 0;
+  set_t1_strips(&g, pl->logNp);
   Spectral sp = pl->spec;
   sp.conj = conj ? 1 : 0;
   {
@@ -1039,6 +1040,7 @@ nuasm_status run_type2_pipeline(nuasm_plan_s* pl, PointSet& q, const float2* pla
   GridGeom g = pl->geom;
   g.Nin = Nin;
   g.crop = 0;
+  set_t2_strips(&g, pl->logNpf, pl->logNp);
   Spectral sp = pl->spec;
   sp.conj = conj ? 1 : 0;
   {
@@ -1067,6 +1069,7 @@ nuasm_status run_type3_pipeline(nuasm_plan_s* pl, PointSet& src, PointSet& dst, 
   if (s != NUASM_OK) return s;
   GridGeom g = pl->geom;
   g.crop = 0;
+  set_t3_strips(&g, pl->logNpf);
   Spectral sp = pl->spec;
   sp.conj = conj ? 1 : 0;
   {
