@@ -307,6 +307,20 @@ __device__ __forceinline__ float es_kernel_fast(float d, float two_over_w, float
   return r > 0.0f ? __builtin_amdgcn_exp2f(beta_log2e * (__builtin_amdgcn_sqrtf(r) - 1.0f)) : 0.0f;
 }
 
+// The weights of all W taps of one axis with one or two operations less each:
+// d is the first tap's offset, tap m lies at d + m.
+template <int W>
+__device__ __forceinline__ void es_weights(float d, float two_over_w, float beta_log2e, float (&w)[W]) {
+  const float u = d * two_over_w;
+#pragma unroll
+  for (int m = 0; m < W; ++m) {
+    const float t = fmaf((float)m, two_over_w, u);
+    const float r = fmaf(-t, t, 1.0f);
+    const float e = __builtin_amdgcn_exp2f(fmaf(beta_log2e, __builtin_amdgcn_sqrtf(r), -beta_log2e));
+    w[m] = r > 0.0f ? e : 0.0f;
+  }
+}
+
 // Bin record: one (point, bin) pair.  lx, ly: first tap relative to the bin
 // origin (int8 each), bit 16: the bin holds the point's first tap; dx, dy:
 // offset of the first tap from the point in fine cells; idx: caller's point
