@@ -1,8 +1,8 @@
 // Rayleigh-Sommerfeld diffraction by direct summation over point pairs
 // (Eq. 10 with the integral over the source replaced by a weighted sum), the
 // accuracy reference the paper measures NU-ASM and NU-FRE against.  O(M1 M2)
-// and bound by the vector ALUs: every pair costs a square root, a
-// reciprocal, a sine and a cosine.
+// and bound by the vector ALUs: every pair costs a square root, a sine and a
+// cosine, and a float64 phase.
 //
 // Work split on gfx950: one workgroup holds 64 destinations (one per lane)
 // and eight waves; each wave sums an eighth of the sources, read with scalar
@@ -15,34 +15,63 @@ namespace nuasm {
 
 constexpr int kRsWaves = 8;   // waves per workgroup, each over an eighth of the sources
 constexpr int kRsBlock = 64;  // sources per float32 partial sum (then added in float64)
+constexpr double kRsNear = 1e5;  // largest |z|/l summed by the shorter form of the phase
 constexpr int kRsUnroll = 8;  // sources whose scalar loads are issued together
 
-// One pair's term of the sum, without the source weight:
-// (z/r)(1 - i k r) exp(i k r)/r^2 with r = sqrt(rho^2 + z^2).
-// The phase k r / (2 pi) = |z|/l + (r - |z|)/l is formed in float64 as
-// c0 + rho^2 / (l |z| (1 + s)), s = r/|z| = sqrt(1 + rho^2/z^2), where c0 is
-// |z|/l reduced mod 1 on the host: no cancellation in r - |z| and no large
-// argument.  s and 1/(1 + s) come from the float32 hardware estimates refined
-// by one float64 Newton step each (relative error ~1e-14, i.e. ~1e-11 cycles
-// at 1000 cycles of phase).  The amplitude needs float32 only:
-// z/r^3 = (z/|z|^3) y^3 and k z/r^2 = (k z/z^2) y^2 with y = |z|/r.
-__device__ __forceinline__ float2 rs_term(double rho2, const RsConst& k) {
-  const double u = fma(rho2, k.inv_z2, 1.0);
-  double y = (double)__builtin_amdgcn_rsqf((float)u);
-  y = y * fma(-0.5 * u, y * y, 1.5);          // 1/sqrt(u) = |z|/r
-  const double d = fma(u, y, 1.0);            // 1 + r/|z|
-  double q = (double)__builtin_amdgcn_rcpf((float)d);
-  q = q * fma(-d, q, 2.0);                    // 1/(1 + r/|z|)
-  double cyc = fma(rho2 * k.inv_lz, q, k.c0);
-  cyc -= rint(cyc);
+// One pair's term of the sum, w (z/r)(1 - i k r) exp(i k r)/r^2 with
+// r = sqrt(rho^2 + z^2), divided by k z/z^2 (the caller multiplies the sum).
+// (dx, dy) is the pair's distance over |z| and s = r/|z| = sqrt(u),
+// u = 1 + dx^2 + dy^2.
+//
+// FAR = false, |z|/l <= kRsNear: the phase k r / (2 pi) = (|z|/l) s is formed
+// in float64 and reduced by whole cycles before the float32 sine and cosine.
+// s comes from the float32 estimate y0 of 1/sqrt(u) (relative error d <= 1e-7)
+// by one residual correction, s0 = u y0, s = s0 + (u - s0^2) y0/2, whose error
+// is 1.5 d^2 <= 1.4e-14 (1.3e-15 rms): 1.4e-9 cycles at |z|/l = 1e5, a twentieth
+// of the float32 argument's own rounding.  The product with |z|/l is reduced by
+// a fused multiply-add and rounds once.
+// FAR = true: that product would keep too few digits, so (r - |z|)/l is formed
+// without cancellation as rho^2 / (l |z| (1 + s)), 1/(1 + s) from the float32
+// estimate by one Newton step, and |z|/l enters as its fraction c0.
+//
+// The amplitude needs float32 only.  With y = 1/s (corrected: the estimate's
+// error is (u - s0^2) y0^2 / 2), z/r^3 = a3 y^3 and k z/r^2 = ak y^2, the term is
+// ak y^2 ((a3/ak) y - i) (w e).
+// 35 issue slots a pair where the FAR form alone took 43 (an instruction each,
+// two a transcendental): 65536 x 65536 pairs 4.66 -> 3.86 ms
+// (1.11e12 pairs/s, 90 % of vector issue).
+template <bool FAR>
+__device__ __forceinline__ void rs_add(double dx, double dy, float2 w, const RsConst& k, float& sr, float& si) {
+  const double rho2 = fma(dx, dx, dy * dy);
+  const double u = FAR ? 1.0 + rho2 : fma(dx, dx, fma(dy, dy, 1.0));
+  const float y0f = __builtin_amdgcn_rsqf((float)u);
+  const double y0 = (double)y0f;
+  double cyc;
+  float yf;
+  if constexpr (FAR) {
+    const double y = y0 * fma(-0.5 * u, y0 * y0, 1.5);
+    const double d = fma(u, y, 1.0);
+    double q = (double)__builtin_amdgcn_rcpf((float)d);
+    q = q * fma(-d, q, 2.0);
+    cyc = fma(rho2 * k.zl, q, k.c0);
+    cyc -= rint(cyc);
+    yf = (float)y;
+  } else {
+    const double s0 = u * y0;
+    const double eh = fma(-s0, s0, u) * (0.5 * y0);
+    const double s = s0 + eh;
+    cyc = fma(k.zl, s, -rint(k.zl * s));
+    yf = fmaf((float)eh, y0f * y0f, y0f);
+  }
   const float2 e = cis_rev((float)cyc);
-  const float yf = (float)y;
-  const float y2 = yf * yf;
-  const float ar = k.a3 * y2 * yf;            // z / r^3
-  const float ai = -k.ak * y2;                // -k z / r^2
-  return make_float2(ar * e.x - ai * e.y, ar * e.y + ai * e.x);
+  const float y2 = yf * yf, b = k.ratio * yf;
+  // P = w e; P (b - i) = (P.x b + P.y, P.y b - P.x)
+  const float pr = fmaf(w.x, e.x, -(w.y * e.y)), pi = fmaf(w.x, e.y, w.y * e.x);
+  sr = fmaf(fmaf(pr, b, pi), y2, sr);
+  si = fmaf(fmaf(pi, b, -pr), y2, si);
 }
 
+template <bool FAR>
 __global__ void __launch_bounds__(64 * kRsWaves)
 k_rs_direct(const double* __restrict__ x1, const double* __restrict__ y1, const float2* __restrict__ c,
             int64_t M1, const double* __restrict__ x2, const double* __restrict__ y2, int64_t M2, RsConst k,
@@ -52,18 +81,15 @@ k_rs_direct(const double* __restrict__ x1, const double* __restrict__ y1, const 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t j = (int64_t)blockIdx.x * 64 + lane;
   const bool live = j < M2;
-  const double X = (live ? x2[j] : 0.0) + k.ox;
-  const double Y = (live ? y2[j] : 0.0) + k.oy;
+  const double X = ((live ? x2[j] : 0.0) + k.ox) * k.inv_az;
+  const double Y = ((live ? y2[j] : 0.0) + k.oy) * k.inv_az;
   const int64_t per = (M1 + kRsWaves - 1) / kRsWaves;
   const int64_t i0 = min(M1, (int64_t)wave * per);
   const int64_t i1 = min(M1, i0 + per);
   double accr = 0.0, acci = 0.0;
   float sr = 0.f, si = 0.f;
   auto pair = [&](double sx, double sy, float2 w) {
-    const double dx = X - sx, dy = Y - sy;
-    const float2 t = rs_term(fma(dx, dx, dy * dy), k);
-    sr = fmaf(w.x, t.x, fmaf(-w.y, t.y, sr));
-    si = fmaf(w.x, t.y, fmaf(w.y, t.x, si));
+    rs_add<FAR>(fma(-sx, k.inv_az, X), fma(-sy, k.inv_az, Y), w, k, sr, si);
   };
   int64_t i = i0;
   // full groups of kRsUnroll sources: their scalar loads are issued together
@@ -100,7 +126,7 @@ k_rs_direct(const double* __restrict__ x1, const double* __restrict__ y1, const 
       r += part[w][lane].x;
       i += part[w][lane].y;
     }
-    out[j] = make_float2((float)(r * k.inv_2pi), (float)(i * k.inv_2pi));
+    out[j] = make_float2((float)(r * k.scale), (float)(i * k.scale));
   }
 }
 
@@ -108,8 +134,12 @@ hipError_t launch_rs_direct(const double* x1, const double* y1, const float2* c,
                             const double* y2, int64_t M2, const RsConst& k, float2* out, hipStream_t st) {
   if (M2 <= 0) return hipSuccess;
   const int64_t grid = (M2 + 63) / 64;
-  hipLaunchKernelGGL(k_rs_direct, dim3((unsigned)grid), dim3(64 * kRsWaves), 0, st, x1, y1, c, M1, x2, y2, M2, k,
-                     out);
+  if (k.zl <= kRsNear)
+    hipLaunchKernelGGL(k_rs_direct<false>, dim3((unsigned)grid), dim3(64 * kRsWaves), 0, st, x1, y1, c, M1, x2, y2,
+                       M2, k, out);
+  else
+    hipLaunchKernelGGL(k_rs_direct<true>, dim3((unsigned)grid), dim3(64 * kRsWaves), 0, st, x1, y1, c, M1, x2, y2,
+                       M2, k, out);
   return hipGetLastError();
 }
 

@@ -1730,12 +1730,11 @@ nuasm_status nuasm_rs_direct(int64_t M1, const double* x1, const double* y1, con
   RsConst kc{};
   kc.ox = ox;
   kc.oy = oy;
-  kc.inv_z2 = 1.0 / (z * z);
-  kc.inv_lz = 1.0 / (lambda * az);
+  kc.inv_az = 1.0 / az;
+  kc.zl = zl;
   kc.c0 = zl - std::nearbyint(zl);
-  kc.inv_2pi = 1.0 / (2.0 * kPi);
-  kc.a3 = (float)(z / (az * az * az));
-  kc.ak = (float)(k * z / (z * z));
+  kc.scale = k * z / (z * z) / (2.0 * kPi);
+  kc.ratio = (float)(1.0 / (k * az));
   HIP_TRY(launch_rs_direct(x1, y1, (const float2*)c, M1, x2, y2, M2, kc, (float2*)out, (hipStream_t)stream),
           "launch rs_direct");
   return NUASM_OK;
