@@ -148,6 +148,19 @@ constexpr int kWgRec = 0, kWgMulti = 1, kWgSlot = 2, kWgSp = 3, kWgIp = 3 + kCla
 constexpr int kWgVals = 3 + 2 * kClasses;  // 11
 static_assert(kWgVals <= kBinPre, "per-bin prefixes fit the table row");
 
+// The six counts, for the later kernels and for the host.  (Writing them to
+// pinned memory here spares a synchronous set_points the copy behind its last
+// launch, 2 to 4 us and as much again to start it.)
+__device__ __forceinline__ void write_counts(const BinScanOut& so, int nsp, int nip, int records, int multi,
+                                             int rejected, int slots) {
+  const int v[6] = {nsp, nip, records, multi, rejected, slots};
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    so.nch[i] = v[i];
+    if (so.status) so.status[i] = v[i];
+  }
+}
+
 // size class of a bin of c records split into chunks of at most `chunk`:
 // 3 for a full chunk, 2 for at least half, 1 for at least an eighth, else 0
 __device__ __forceinline__ int size_class(int c, int chunk) {
@@ -312,12 +325,7 @@ __device__ __forceinline__ void bin_scan_body(const ColscanArgs& a, int bid, int
       nsp_all += tot[kWgSp + k];
       nip_all += tot[kWgIp + k];
     }
-    so.nch[0] = nsp_all;
-    so.nch[1] = nip_all;
-    so.nch[2] = tot[kWgRec];
-    so.nch[3] = tot[kWgMulti];
-    so.nch[4] = total[T];
-    so.nch[5] = tot[kWgSlot];
+    write_counts(so, nsp_all, nip_all, tot[kWgRec], tot[kWgMulti], total[T], tot[kWgSlot]);
   }
   if (bb >= T) return;
   const int spc = so.sp_chunk, ipc = so.ip_chunk;
@@ -528,14 +536,7 @@ __device__ __forceinline__ void bin_tables(int T, const BinScanOut& so, int reje
       nsp_all += tot[kWgSp + k];
       nip_all += tot[kWgIp + k];
     }
-    if (b == 0) {
-      so.nch[0] = nsp_all;
-      so.nch[1] = nip_all;
-      so.nch[2] = tot[kWgRec];
-      so.nch[3] = tot[kWgMulti];
-      so.nch[4] = rejected;
-      so.nch[5] = tot[kWgSlot];
-    }
+    if (b == 0) write_counts(so, nsp_all, nip_all, tot[kWgRec], tot[kWgMulti], rejected, tot[kWgSlot]);
     if (b < T) {
       const int rec0 = v[kWgRec], slot0 = v[kWgSlot];
       base(b, rec0);

@@ -89,6 +89,8 @@ struct BinScanOut {
   int4* ip_chunks;   // interpolation chunks
   int* nch;          // spread chunks, interp chunks, records, multi bins, points out of range,
                      // partial-tile slots of split bins
+  int* status;       // the same six in pinned host memory, where a synchronous
+                     // set_points reads them once its stream has finished; or null
   int* bin_pre;      // [T][kBinPre] per-bin prefixes inside the bin's column-scan workgroup
   int* wg_sum;       // [bin_scan_workgroups(T)][kBinPre] that workgroup's sums
   int sp_chunk;      // max records per spreading chunk

@@ -269,6 +269,7 @@ struct PointSet {
   int64_t scratch_chunks = 0;  // tiles it holds
   size_t scratch_bytes = 0;
   int* host_stat = nullptr;  // pinned [8]
+  int* dev_stat = nullptr;   // its device address
   int64_t M = 0;
   bool ready = false;
   bool synced = false;
@@ -489,6 +490,7 @@ nuasm_status alloc_point_set(nuasm_plan_s* pl, PointSet& q) {
   HIP_TRY(dalloc(pl, &q.wg_sum, (size_t)bin_scan_workgroups(pl->T) * kBinPre), "hipMalloc(bins)");
   HIP_TRY(dalloc(pl, &q.nch, (size_t)8), "hipMalloc(counters)");
   HIP_TRY(host_malloc((void**)&q.host_stat, sizeof(int) * 8), "hipHostMalloc(status)");
+  HIP_TRY(hipHostGetDevicePointer((void**)&q.dev_stat, q.host_stat, 0), "hipHostGetDevicePointer");
   HIP_TRY(launch_fill_i32(q.nch, 0, 8, pl->stream), "launch fill");
   return NUASM_OK;
 }
@@ -644,7 +646,7 @@ void free_bin_arrays(nuasm_plan_s* pl, PointSet& q) {
   f(q.nch, sizeof(int) * 8);
   q.counts = q.cursor = q.sp_first = q.sp_n = q.multi = q.bin_pre = q.wg_sum = q.nch = nullptr;
   if (q.host_stat) (void)host_free(q.host_stat);
-  q.host_stat = nullptr;
+  q.host_stat = q.dev_stat = nullptr;
 }
 
 // The bin side and everything that follows from it (bins per axis, the
@@ -809,9 +811,10 @@ nuasm_status bind_points(nuasm_plan_s* pl, PointSet& q, int64_t M, const double*
   hipStream_t st = pl->stream;
   // With stage timing on, the binning keeps its four launches, each timed;
   // the records and tables are the same.
+  int* status = (pl->p.flags & NUASM_DEFER_RANGE_CHECK) ? nullptr : q.dev_stat;
   const bool fused = M > 0 && !stable_bins(pl) && !pl->timing && bin_scan_in_scatter(pl->T);
   if (fused) {
-    BinScanOut so{q.cursor, q.sp_chunks, q.sp_first, q.sp_n, q.multi, q.ip_chunks, q.nch,
+    BinScanOut so{q.cursor, q.sp_chunks, q.sp_first, q.sp_n, q.multi, q.ip_chunks, q.nch, status,
                   nullptr, nullptr, q.sp_chunk, q.ip_chunk};
     if (M <= kBinSmall && pl->bin_ppw == 0) {
       StageScope sc(pl, NUASM_STAGE_BIN_SCATTER);
@@ -841,7 +844,7 @@ nuasm_status bind_points(nuasm_plan_s* pl, PointSet& q, int64_t M, const double*
     {
       // column scan, then bin scan; with no points (G = 0) they write zero
       // totals and empty-bin chunk tables
-      const BinScanOut so{q.cursor, q.sp_chunks, q.sp_first, q.sp_n, q.multi, q.ip_chunks, q.nch,
+      const BinScanOut so{q.cursor, q.sp_chunks, q.sp_first, q.sp_n, q.multi, q.ip_chunks, q.nch, status,
                           q.bin_pre, q.wg_sum, q.sp_chunk, q.ip_chunk};
       {
         StageScope sc(pl, NUASM_STAGE_BIN_COLSCAN);
@@ -861,7 +864,7 @@ nuasm_status bind_points(nuasm_plan_s* pl, PointSet& q, int64_t M, const double*
     q.ready = true;
     return NUASM_OK;
   }
-  HIP_TRY(hipMemcpyAsync(q.host_stat, q.nch, sizeof(int) * 6, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+  // the counts have reached the host (BinScanOut::status) when the stream has finished
   HIP_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
   {
     const nuasm_status ps = point_status(q, &q == &pl->ps[1] ? 1 : 0);
