@@ -1059,15 +1059,12 @@ __device__ __forceinline__ void spread_body(const SpreadArgs& a, int bid, int) {
 // accumulator element e of lane l is D[4 (l / 16) + e][l % 16].
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-struct __align__(16) MfmaRec {
-  float cr, ci;  // the point's value
-  int lxy;       // first tap relative to the bin origin: column (low 16 bits), row (high)
-  int pad;
-};
-
 // Sub-batches of 256 records (one per thread), loaded one ahead: the LDS
-// footprint (about 24 KB at w = 7) and the registers leave room for six
-// workgroups per CU, which hide the load and LDS latencies.
+// footprint (26 KB at w = 7) and the registers leave room for six
+// workgroups per CU, which hide the load and LDS latencies.  Vector issue and
+// the matrix instructions, which share it, bound the launch (55 and 32
+// thousand cycles a SIMD of about 105 at 2^20 clustered points): 52.8 -> 50.1
+// us with rows of odd length and the first taps in the list entries.
 constexpr int kMfmaSB = kSpreadSubBatch;
 static_assert(kMfmaSB == kSpreadThreads, "one record per thread");
 
@@ -1084,17 +1081,20 @@ __device__ __forceinline__ void spread_mfma_body(const SpreadArgs& a, int bid, i
   constexpr int QPW = NQ / NWV;                // quarter tiles per wave: 1 (32 x 32 bins) or 4 (64 x 64)
   constexpr int NACC = QPW == 1 ? 2 : 1;       // accumulator pairs per quarter tile
   static_assert(NQ % NWV == 0, "whole quarter tiles per wave");
-  // one LDS row per record: its MfmaRec, then its x weights and its y
-  // weights, each with a zero on either side (tap m at 1 + m), so that an
-  // operand is one read at a clamped tap index.  The lists hold row byte
-  // offsets.  Record SB is a sentinel (zero value and weights) that pads the
-  // lists to whole steps.
+  // one LDS row per record: its value, its x weights and its y weights, the
+  // weights with a zero on either side (tap m at 1 + m), so that an operand is
+  // one read at a clamped tap index.  The row length is odd, so that the 64
+  // lanes staging a column of the rows, and the four records of a group, fall
+  // on different banks (24 floats a row: 8-way conflicts in the staging).  A
+  // list entry holds a row's byte offset and, a byte each, the record's first
+  // tap relative to the quarter tile.  Record SB is a sentinel (zero value and
+  // weights) that pads the lists to whole steps.
   constexpr int WP = W + 2, STEP = 4 * NACC;
-  constexpr int RX = 4, RY = 4 + WP;                 // floats: x and y weights in a row
-  constexpr int RSZ = (4 + 2 * WP + 3) / 4 * 4;      // row length, whole 16-byte units
+  constexpr int RX = 2, RY = 2 + WP;       // floats: x and y weights in a row
+  constexpr int RSZ = (2 + 2 * WP) | 1;    // row length
   static_assert((SB + 1) * RSZ * 4 < 65536, "row offsets fit 16 bits");
-  __shared__ __align__(16) float srow[(SB + 1) * RSZ];
-  __shared__ unsigned short slist[NQ][SB + 2 * STEP];
+  __shared__ float srow[(SB + 1) * RSZ];
+  __shared__ unsigned slist[NQ][SB + 2 * STEP];
   __shared__ int scnt[NWV][NQ];
   __shared__ int sbase[NWV][NQ];
   __shared__ int slen[NQ];
@@ -1148,13 +1148,9 @@ __device__ __forceinline__ void spread_mfma_body(const SpreadArgs& a, int bid, i
     if (ok) {
       lx = rec_lx(rc.packed);
       ly = rec_ly(rc.packed);
-      MfmaRec m;
-      m.cr = cv.x;
-      m.ci = cv.y;
-      m.lxy = (lx & 0xffff) | (ly << 16);
-      m.pad = 0;
       float* row = srow + t * RSZ;
-      *reinterpret_cast<MfmaRec*>(row) = m;
+      row[0] = cv.x;
+      row[1] = cv.y;
 #pragma unroll
       for (int mm = 0; mm < W; ++mm) {
         row[RX + 1 + mm] = es_kernel_fast(rc.dx + (float)mm, a.two_over_w, blog);
@@ -1181,13 +1177,17 @@ __device__ __forceinline__ void spread_mfma_body(const SpreadArgs& a, int bid, i
         run += c2;
       }
       const int padded = (run + STEP - 1) / STEP * STEP;
-      for (int p = run; p < padded; ++p) slist[t][p] = (unsigned short)(SB * RSZ * 4);
+      for (int p = run; p < padded; ++p) slist[t][p] = (unsigned)(SB * RSZ * 4);
       slen[t] = padded;
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
-      if (rank[q] >= 0) slist[q][sbase[wv][q] + rank[q]] = (unsigned short)(t * RSZ * 4);
+    for (int q = 0; q < NQ; ++q) {
+      const int qx = 16 * (q % QS), qy = 16 * (q / QS);
+      if (rank[q] >= 0)
+        slist[q][sbase[wv][q] + rank[q]] =
+            (unsigned)(t * RSZ * 4) | ((unsigned)((lx - qx) & 0xff) << 16) | ((unsigned)((ly - qy) & 0xff) << 24);
+    }
     __syncthreads();
     const float2 nv = a.vals[nx.idx];
     // the wave's quarter tiles: groups of four listed records, NACC groups
@@ -1196,36 +1196,33 @@ __device__ __forceinline__ void spread_mfma_body(const SpreadArgs& a, int bid, i
 #pragma unroll
     for (int u = 0; u < QPW; ++u) {
       const int q = wv * QPW + u;
-      const int sx0 = 16 * (q % QS), sy0 = 16 * (q / QS);
       const int len = __builtin_amdgcn_readfirstlane(slen[q]);  // uniform: a scalar loop
-      const int oy = sy0 + ii + 1, ox = sx0 + ii + 1;
+      const int i1 = ii + 1;
       const char* base = reinterpret_cast<const char*>(srow);
       // the list entries of the next step are read one step ahead (the list
       // has room for the reads past its end; those values go unused)
-      int off[NACC];
+      unsigned ent[NACC];
 #pragma unroll
-      for (int h = 0; h < NACC; ++h) off[h] = slist[q][4 * h + kk];
+      for (int h = 0; h < NACC; ++h) ent[h] = slist[q][4 * h + kk];
       for (int g = 0; g < len; g += STEP) {
-        const char* rp[NACC];
+        float cr[NACC], ci[NACC], ay[NACC], bx[NACC];
 #pragma unroll
         for (int h = 0; h < NACC; ++h) {
-          rp[h] = base + off[h];
-          off[h] = slist[q][g + STEP + 4 * h + kk];
-        }
-        MfmaRec m[NACC];
-#pragma unroll
-        for (int h = 0; h < NACC; ++h) m[h] = *reinterpret_cast<const MfmaRec*>(rp[h]);
-#pragma unroll
-        for (int h = 0; h < NACC; ++h) {
-          const int mlx = (int)(short)(m[h].lxy & 0xffff), mly = m[h].lxy >> 16;
+          const unsigned en = ent[h];
+          ent[h] = slist[q][g + STEP + 4 * h + kk];
           // tap index of this row / column, clamped onto a zero pad outside
-          const int ty = min(max(oy - mly, 0), W + 1);
-          const int tx = min(max(ox - mlx, 0), W + 1);
-          const float* wr = reinterpret_cast<const float*>(rp[h]);
-          const float ay = wr[RY + ty];
-          const float bx = wr[RX + tx];
-          accr[u][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(m[h].cr * ay, bx, accr[u][h], 0, 0, 0);
-          acci[u][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(m[h].ci * ay, bx, acci[u][h], 0, 0, 0);
+          const int ty = min(max(i1 - ((int)en >> 24), 0), W + 1);
+          const int tx = min(max(i1 - (int)(signed char)(en >> 16), 0), W + 1);
+          const float* row = reinterpret_cast<const float*>(base + (en & 0xffff));
+          cr[h] = row[0];
+          ci[h] = row[1];
+          ay[h] = row[RY + ty];
+          bx[h] = row[RX + tx];
+        }
+#pragma unroll
+        for (int h = 0; h < NACC; ++h) {
+          accr[u][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(cr[h] * ay[h], bx[h], accr[u][h], 0, 0, 0);
+          acci[u][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(ci[h] * ay[h], bx[h], acci[u][h], 0, 0, 0);
         }
       }
     }
