@@ -79,8 +79,9 @@ def counter_record(stage: str):
 _STAGE_OF_BODY = (
     ("bin_hist_body", "bin_hist"), ("bin_colscan_body", "bin_colscan"), ("bin_scan_body", "bin_scan"),
     ("bin_scatter_det_body", "bin_scatter"),
-    ("bin_scatter_body", "bin_scatter"), ("spread_mfma_body", "spread"), ("spread_reduce_body", "spread_reduce"),
-    ("spread_body", "spread"), ("interp_body", "interp"), ("t1_rows_inv_body", "t1_rows_inv"),
+    ("bin_scatter_scan_body", "bin_scatter"), ("bin_scatter_body", "bin_scatter"), ("spread_mfma_body", "spread"),
+    ("spread_reduce_body", "spread_reduce"), ("spread_body", "spread"), ("interp_body", "interp"),
+    ("t1_rows_inv_body", "t1_rows_inv"), ("t1_rows_inv_crop_body", "t1_rows_inv"),
     ("t1_rows_body", "t1_rows"), ("t1_cols_body", "t1_cols"), ("t2_rows_inv_body", "t2_rows_inv"),
     ("t2_rows_body", "t2_rows"), ("t2_cols_body", "t2_cols"), ("copyBuffer", "copy"))
 
