@@ -52,3 +52,28 @@ def test_bins_in_point_order(P, N, tile, M, kind):
     assert np.all(np.diff(key) > 0)  # by bin, then by point
     order = np.lexsort((rn[:, 3], bn))
     assert np.array_equal(bd, bn[order]) and np.array_equal(rd, rn[order])
+
+
+@pytest.mark.parametrize("N,M,kind", [(64, 70, "one bin"), (64, 71, "one bin"), (64, 72, "one bin"),
+                                      (32, 61113, "uniform"), (64, 20000, "uniform"), (256, 9000, "three_clusters")])
+def test_long_runs_in_point_order(P, N, M, kind):
+    """Runs of a range around the length from which a run is ranked by bits,
+    and many long runs that begin at any position."""
+    geo = geometry(N=N, g=4e-6, lam=633e-9, z=0.01, tf="asm", band="full")
+    rng = np.random.default_rng(M)
+    if kind == "one bin":
+        x, y = (rng.uniform(0.2, 3.0, M) * geo.g for _ in range(2))
+    elif kind == "uniform":
+        x, y = (rng.uniform(-0.5, 0.5, M) * N * geo.g for _ in range(2))
+    else:
+        c = rng.integers(0, 3, M)
+        x, y = (rng.normal(np.array([-0.3, 0.0, 0.25])[c], 0.02).clip(-0.5, 0.5) * N * geo.g for _ in range(2))
+    xd, yd = dev(torch, x), dev(torch, y)
+    got = []
+    for det in (True, False):
+        p = make_plan(P, geo, 1, deterministic=det)
+        got.append(_records(p.set_points(xd, yd)))
+        p.close()
+    (rd, bd), (rn, bn) = got
+    order = np.lexsort((rn[:, 3], bn))
+    assert np.array_equal(bd, bn[order]) and np.array_equal(rd, rn[order])
