@@ -670,7 +670,10 @@ __device__ __forceinline__ void bin_scatter_scan_body(const BinScatterArgs& sa, 
 // serial steps: 4096 points on 25 bins take 11.8 us, against 4.8 + 5.6 + 3.1 +
 // 6.5 us in four launches (8.3 + 3.7 + 6 in three).  Up to kBinSmall points,
 // one range of the general path (4 points a thread), beyond which a second CU
-// would help.
+// would help, and up to kBinSmallBins bins: the tables of more are better
+// written by several workgroups (a whole binning of 4096 points, one launch and
+// three: 11.3 and 15.2 us on 25 bins, 15.2 and 16.2 on 1089, 35.0 and 21.2 on
+// 4225).
 __device__ __forceinline__ void bin_small_body(const BinScatterArgs& sa, int, int) {
   const BinArgs& a = sa.b;
   const BinGeom& g = a.g;
@@ -1556,7 +1559,7 @@ hipError_t launch_bin_scatter_scan(const double* x, const double* y, int64_t M, 
 hipError_t launch_bin_small(const double* x, const double* y, int64_t M, BinGeom g, int* total, const BinScanOut& so,
                             BinRec* recs, int* rej_end, hipStream_t st) {
   const int T = g.TX * g.TX;
-  if (!bin_scan_in_scatter(T) || M < 1 || M > kBinSmall) return hipErrorInvalidValue;
+  if (T > kBinSmallBins || !bin_scan_in_scatter(T) || M < 1 || M > kBinSmall) return hipErrorInvalidValue;
   return launch_or_record<BinScatterArgs, bin_small_body, kBinThreads>(
       scatter_args(x, y, M, g, 0, nullptr, total, so, recs, rej_end), 1, (T + 1) * 4, st);
 }

@@ -188,6 +188,7 @@ hipError_t launch_fill_i32(int* p, int v, int64_t n, hipStream_t st);
 // counting sort of (point, bin) pairs: hist -> colscan -> scan -> scatter
 constexpr int kBinPointsMax = 65535;  // points per binning workgroup (16-bit LDS counters)
 constexpr int kBinSmall = 4096;        // most points binned by one workgroup
+constexpr int kBinSmallBins = 2048;    // and most bins, two a thread
 constexpr int kBinPointsStable = 1024;  // the same in deterministic mode (stable scatter in LDS)
 // hist rows and offset rows have T + 1 entries (entry T: points outside the window)
 hipError_t launch_bin_hist(const double* x, const double* y, int64_t M, BinGeom g, int ppw, int G,

@@ -816,7 +816,7 @@ nuasm_status bind_points(nuasm_plan_s* pl, PointSet& q, int64_t M, const double*
   if (fused) {
     BinScanOut so{q.cursor, q.sp_chunks, q.sp_first, q.sp_n, q.multi, q.ip_chunks, q.nch, status,
                   nullptr, nullptr, q.sp_chunk, q.ip_chunk};
-    if (M <= kBinSmall && pl->bin_ppw == 0) {
+    if (M <= kBinSmall && pl->T <= kBinSmallBins && pl->bin_ppw == 0) {
       StageScope sc(pl, NUASM_STAGE_BIN_SCATTER);
       HIP_TRY(launch_bin_small(x, y, M, pl->bgeom, q.counts, so, q.recs, rej_end(q), st), "launch bin_small");
     } else {
