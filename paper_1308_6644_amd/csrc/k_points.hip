@@ -1329,7 +1329,12 @@ __device__ __forceinline__ void spread_reduce_body(const SpreadReduceArgs& a, in
 // in order of their first tap's row and group of columns (a counting sort in
 // LDS, 256 keys): the lanes of a wave then read neighbouring cells of a row,
 // equal ones as one (13 cycles).  A batch of few records is spread too thin to
-// gain and is taken as it is.  Same sums either way, in the same order.
+// gain and is taken as it is, and so is every batch of fewer than
+// kInterpSortTaps taps an axis, whose gather costs less than the sort (without
+// and with it, 1943215 points on 528 x 528 cells: w = 7 49.4 and 35.8 us, 6
+// 38.8 and 33.4, 5 32.5 and 33.2, 4 30.0 and about 34; 2^20 clustered on
+// 2064 x 2064: 32.2 and 28.7, 26.9 and 27.3, 25.1 and 26.3).  Same sums either
+// way, in the same order.
 // w = 7: 2^24 points (4 a cell) 356 -> 301 us, 2^22 in three clusters 108 ->
 // 99, 2^20 clustered 32.2 -> 27.5.  At 2^24 points the 8-byte stores in caller
 // order (a 64-byte write each between the L2s and the Infinity Cache) are the
@@ -1337,6 +1342,7 @@ __device__ __forceinline__ void spread_reduce_body(const SpreadReduceArgs& a, in
 constexpr int kInterpThreads = 256;
 constexpr int kInterpBatch = 4;
 constexpr int kInterpSortMin = 384;  // records from which a batch is sorted
+constexpr int kInterpSortTaps = 6;   // and taps an axis
 static_assert(kInterpSortMin <= kInterpThreads * kInterpBatch, "an unsorted batch is the last one");
 // (launch bound: at least 5 waves per SIMD, i.e. at most 96 VGPRs)
 
@@ -1347,7 +1353,8 @@ __device__ __forceinline__ void interp_body(const InterpArgs& a, int bid, int nb
   constexpr int NT = kInterpThreads, B = kInterpBatch, NWV = NT / 64;
   constexpr int TL = TILE == 64 ? 6 : 5;
   __shared__ __align__(16) float2 sg[RS * RSP];
-  __shared__ BinRec srec[NT * B];
+  constexpr bool SORT = W >= kInterpSortTaps;
+  __shared__ BinRec srec[SORT ? NT * B : 1];
   __shared__ int hist[NT], wsum[NWV];
   const int cid = bid;
   // the chunk count and the descriptor requested together (the launch grid
@@ -1417,6 +1424,15 @@ __device__ __forceinline__ void interp_body(const InterpArgs& a, int bid, int nb
     }
     a.out[r.idx] = make_float2(accr, acci);
   };
+  if constexpr (!SORT) {
+    for (int r0 = 0; r0 < n; r0 += NT * B) {
+      if (r0 > 0) load(r0);
+#pragma unroll
+      for (int q = 0; q < B; ++q)
+        if (r0 + t + q * NT < n && rec_primary(rl[q].packed)) gather(rl[q]);
+    }
+    return;
+  }
   for (int r0 = 0; r0 < n; r0 += NT * B) {
     if (n - r0 <= kInterpSortMin) {  // uniform; the chunk's last batch
 #pragma unroll
