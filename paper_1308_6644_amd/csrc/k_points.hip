@@ -1333,8 +1333,12 @@ __device__ __forceinline__ void spread_reduce_body(const SpreadReduceArgs& a, in
 // kInterpSortTaps taps an axis, whose gather costs less than the sort (without
 // and with it, 1943215 points on 528 x 528 cells: w = 7 49.4 and 35.8 us, 6
 // 38.8 and 33.4, 5 32.5 and 33.2, 4 30.0 and about 34; 2^20 clustered on
-// 2064 x 2064: 32.2 and 28.7, 26.9 and 27.3, 25.1 and 26.3).  Same sums either
-// way, in the same order.
+// 2064 x 2064: 32.2 and 28.7, 26.9 and 27.3, 25.1 and 26.3).  Nor is anything
+// sorted in a launch of fewer than kInterpSortChunks chunks, five for four CUs:
+// with a workgroup or so to a CU the LDS keeps up, and the sort is latency on
+// its longest chunk (w = 7, clustered, without and with: 60000 points at N = 64
+// 7.4 and 8.3 us, 500000 at N = 256 19.4 and 20.8, 10^6 29.0 and 24.6).  Same
+// sums either way, in the same order.
 // w = 7: 2^24 points (4 a cell) 356 -> 301 us, 2^22 in three clusters 108 ->
 // 99, 2^20 clustered 32.2 -> 27.5.  At 2^24 points the 8-byte stores in caller
 // order (a 64-byte write each between the L2s and the Infinity Cache) are the
@@ -1343,7 +1347,7 @@ constexpr int kInterpThreads = 256;
 constexpr int kInterpBatch = 4;
 constexpr int kInterpSortMin = 384;  // records from which a batch is sorted
 constexpr int kInterpSortTaps = 6;   // and taps an axis
-static_assert(kInterpSortMin <= kInterpThreads * kInterpBatch, "an unsorted batch is the last one");
+constexpr int kInterpSortChunks = 320;  // and chunks of the launch
 // (launch bound: at least 5 waves per SIMD, i.e. at most 96 VGPRs)
 
 template <int W, int TILE>
@@ -1424,21 +1428,15 @@ __device__ __forceinline__ void interp_body(const InterpArgs& a, int bid, int nb
     }
     a.out[r.idx] = make_float2(accr, acci);
   };
-  if constexpr (!SORT) {
-    for (int r0 = 0; r0 < n; r0 += NT * B) {
-      if (r0 > 0) load(r0);
-#pragma unroll
-      for (int q = 0; q < B; ++q)
-        if (r0 + t + q * NT < n && rec_primary(rl[q].packed)) gather(rl[q]);
-    }
-    return;
-  }
+  const bool sorted = SORT && nchunks >= kInterpSortChunks;
   for (int r0 = 0; r0 < n; r0 += NT * B) {
-    if (n - r0 <= kInterpSortMin) {  // uniform; the chunk's last batch
+    if (!sorted || n - r0 <= kInterpSortMin) {  // uniform
 #pragma unroll
       for (int q = 0; q < B; ++q)
         if (r0 + t + q * NT < n && rec_primary(rl[q].packed)) gather(rl[q]);
-      break;
+      if (n - r0 <= NT * B) break;
+      load(r0 + NT * B);
+      continue;
     }
     int key[B], rank[B];
 #pragma unroll

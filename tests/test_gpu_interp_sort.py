@@ -51,3 +51,25 @@ def test_batches_after_the_first(P):
     p.set_tuning(interp_chunk=65536)
     got = p.set_points(dev(torch, x), dev(torch, y)).execute(dev(torch, u1))
     check_close(host(got), O.nuasm2(geo, u1, x, y), 1e-5)
+
+
+@pytest.mark.parametrize("tile", [32, 64])
+@pytest.mark.parametrize("tol", [1e-3, 1e-5, 1e-6, 1e-9])
+@pytest.mark.parametrize("M", [319 * 1100, 319 * 1100 + 1, 320 * 1100 + 385, 400 * 1100])
+def test_chunk_count_rule(P, M, tol, tile):
+    """Around the number of chunks from which batches are sorted: bitwise the
+    outputs of a launch of few chunks, which sorts nothing, and those against
+    the oracle at some points."""
+    geo = geometry(N=32, g=4e-6, lam=633e-9, z=0.004, tf="asm", band="full")
+    rng = np.random.default_rng(M + tile)
+    x, y = (rng.uniform(-0.5, 9.0, M) * geo.g for _ in range(2))
+    u1 = synth.unit_phase(rng, (32, 32))
+    xd, yd, ud = dev(torch, x), dev(torch, y), dev(torch, u1)
+    outs = []
+    for chunk in (1100, 65536):
+        p = make_plan(P, geo, 2, tol=tol, forward_only=True)
+        p.set_tuning(interp_chunk=chunk, bin_tile=tile)
+        outs.append(p.set_points(xd, yd).execute(ud))
+    assert torch.equal(outs[0], outs[1])
+    pick = rng.choice(M, size=200, replace=False)
+    check_close(host(outs[0])[pick], O.nuasm2(geo, u1, x[pick], y[pick]), BOUND.get(tol, 10 * tol))
