@@ -318,6 +318,7 @@ struct nuasm_plan_s {
   int sp_method = 0;      // spreading: 0 automatic, 1 register gather, 2 matrix cores
   int nsets = 1;
   size_t bytes = 0;          // device memory the plan allocated itself
+  uint64_t buffers = 0;      // bumped whenever a buffer that launches read or write is freed or moved
   // caller-owned workspace (nuasm_plan_set_workspace): the two grids and the
   // point-count-dependent buffers of every point set are carved from it
   char* ws = nullptr;
@@ -562,6 +563,7 @@ void carve_workspace(nuasm_plan_s* pl) {
 
 // Free the plan-owned grids and point buffers (not a caller's workspace).
 void free_owned_buffers(nuasm_plan_s* pl) {
+  ++pl->buffers;
   auto f = [&](void* p, size_t b) {
     if (p && !pl->ws) {
       (void)dev_free(p);
@@ -629,6 +631,7 @@ nuasm_status bind_workspace(nuasm_plan_s* pl, void* dev, size_t bytes) {
 
 // Free the T-sized bin arrays of a point set (before the bin tile changes).
 void free_bin_arrays(nuasm_plan_s* pl, PointSet& q) {
+  ++pl->buffers;
   const size_t T = (size_t)pl->T;
   auto f = [&](void* p, size_t b) {
     if (p) {
@@ -699,6 +702,7 @@ nuasm_status ensure_points_capacity(nuasm_plan_s* pl, PointSet& q, int64_t M) {
   const int64_t cap = std::max<int64_t>(M, 1024);
   if (cap * 4 > (int64_t)INT32_MAX) return fail(NUASM_ERR_UNSUPPORTED, "too many points (4 M must fit in int32)");
   HIP_TRY(hipStreamSynchronize(pl->stream), "hipStreamSynchronize");
+  ++pl->buffers;
   if (q.recs) {
     (void)dev_free(q.recs);
     pl->bytes -= sizeof(BinRec) * 4 * q.rec_cap;
@@ -758,6 +762,7 @@ nuasm_status ensure_scratch(nuasm_plan_s* pl, PointSet& q) {
   if (pl->ws) return fail(NUASM_ERR_INVALID_ARG, "split-bin scratch exceeds the workspace");
   if (q.scratch) {
     HIP_TRY(hipStreamSynchronize(pl->stream), "hipStreamSynchronize");
+    ++pl->buffers;
     (void)dev_free(q.scratch);
     pl->bytes -= q.scratch_bytes;
     q.scratch = nullptr;
@@ -916,6 +921,7 @@ nuasm_status bind_grid(nuasm_plan_s* pl, PointSet& q, int64_t nx, int64_t ny, do
   if (need > q.gbuf_cap) {
     HIP_TRY(hipStreamSynchronize(pl->stream), "hipStreamSynchronize");
     if (q.gbuf) {
+      ++pl->buffers;
       (void)dev_free(q.gbuf);
       pl->bytes -= sizeof(float2) * q.gbuf_cap;
       q.gbuf = nullptr;
@@ -1768,6 +1774,7 @@ struct BatchGraph {
   char* tables = nullptr;  // device: every grouped stage's entry table and block offsets
   size_t table_bytes = 0;
   std::vector<int64_t> M;    // the point counts it was recorded with
+  std::vector<uint64_t> buffers;  // its planes' buffer generations (nuasm_plan_s::buffers) then
   std::vector<int> slot_of;  // plane -> its completion stamp in ts (0: finished at the start)
 };
 
@@ -1803,6 +1810,7 @@ void drop_graph(BatchGraph& g) {
   g.stages.clear();
   g.table_bytes = 0;
   g.M.clear();
+  g.buffers.clear();
   g.slot_of.clear();
   g.grouped = false;
 }
@@ -2005,7 +2013,10 @@ static hipError_t enqueue_chains(nuasm_batch_s* b, BatchGraph& g, const int* ord
 }
 
 // Launch graph g, or record it first when it is missing or was recorded with
-// other arguments (key).  plane(pl, p) enqueues plane p's work on the plan's
+// other arguments (key) or other buffers of its planes: the three graphs of a
+// batch share these, and a run of one of them with more points (or with fewer,
+// whose smaller chunks need more partial tiles) may have moved what another
+// one's launches point to.  plane(pl, p) enqueues plane p's work on the plan's
 // current stream.  Recording: one eager pass on the caller's stream (sizes every
 // buffer and sets kernel attributes, so that the capture enqueues launches
 // only), then the capture on the internal stream -- stamp, fork onto the
@@ -2022,7 +2033,12 @@ static nuasm_status batch_launch(nuasm_batch_s* b, BatchGraph& g, const std::vec
     HIP_TRY(hipGraphLaunch(g.exec, b->stream), "hipGraphLaunch");
     return NUASM_OK;
   };
-  if (g.exec && key == g.key && g.grouped == b->grouped) return launch();
+  auto generations = [&] {
+    std::vector<uint64_t> v;
+    for (const nuasm_plan_s* pl : b->plans) v.push_back(pl->buffers);
+    return v;
+  };
+  if (g.exec && key == g.key && g.grouped == b->grouped && g.buffers == generations()) return launch();
   if (g.exec && g.grouped && b->grouped && M == g.M) {
     // only buffers changed (the point counts, and so every size and grid, are
     // the ones recorded): collect the new arguments on the host and, when
@@ -2037,6 +2053,7 @@ static nuasm_status batch_launch(nuasm_batch_s* b, BatchGraph& g, const std::vec
       HIP_TRY(hipStreamSynchronize(b->stream), "hipStreamSynchronize");
       HIP_TRY(hipMemcpy(g.tables, host.data(), host.size(), hipMemcpyHostToDevice), "hipMemcpy(grouped tables)");
       g.key = key;
+      g.buffers = generations();
       ++b->refreshed;
       return launch();
     }
@@ -2122,6 +2139,7 @@ static nuasm_status batch_launch(nuasm_batch_s* b, BatchGraph& g, const std::vec
   }
   g.key = key;
   g.M = M;
+  g.buffers = generations();
   ++b->recorded;
   return launch();
 }
