@@ -1765,6 +1765,13 @@ struct GroupedStage {
   std::vector<int> planes;
 };
 
+// What a binning leaves on the host: the point count and the chunk sizes that
+// the launches of a later operator take their grids from.
+struct BoundPoints {
+  int64_t M;
+  int sp_chunk, ip_chunk;
+};
+
 // One recorded graph of a batch and the arguments it was recorded with.
 struct BatchGraph {
   hipGraphExec_t exec = nullptr;
@@ -1775,6 +1782,7 @@ struct BatchGraph {
   size_t table_bytes = 0;
   std::vector<int64_t> M;    // the point counts it was recorded with
   std::vector<uint64_t> buffers;  // its planes' buffer generations (nuasm_plan_s::buffers) then
+  std::vector<BoundPoints> bound;  // per plane, if the graph binds points: a replay binds them again
   std::vector<int> slot_of;  // plane -> its completion stamp in ts (0: finished at the start)
 };
 
@@ -1811,6 +1819,7 @@ void drop_graph(BatchGraph& g) {
   g.table_bytes = 0;
   g.M.clear();
   g.buffers.clear();
+  g.bound.clear();
   g.slot_of.clear();
   g.grouped = false;
 }
@@ -2022,8 +2031,10 @@ static hipError_t enqueue_chains(nuasm_batch_s* b, BatchGraph& g, const int* ord
 // only), then the capture on the internal stream -- stamp, fork onto the
 // branches, every plane on its branch followed by its completion stamp, join.
 // The graph is launched on the caller's stream itself.
+// binds: the graph bins points.  A replay then leaves the planes' host state as
+// the recording did, whatever was bound in between.
 template <typename F>
-static nuasm_status batch_launch(nuasm_batch_s* b, BatchGraph& g, const std::vector<const void*>& key,
+static nuasm_status batch_launch(nuasm_batch_s* b, BatchGraph& g, bool binds, const std::vector<const void*>& key,
                                  const std::vector<int64_t>& M, F plane) {
   const int P = (int)b->plans.size();
   auto launch = [&]() -> nuasm_status {
@@ -2031,6 +2042,13 @@ static nuasm_status batch_launch(nuasm_batch_s* b, BatchGraph& g, const std::vec
     // hops between streams
     b->last = &g;
     HIP_TRY(hipGraphLaunch(g.exec, b->stream), "hipGraphLaunch");
+    for (size_t p = 0; p < g.bound.size(); ++p) {
+      PointSet& q = b->plans[p]->ps[0];
+      q.M = g.bound[p].M;
+      q.sp_chunk = g.bound[p].sp_chunk;
+      q.ip_chunk = g.bound[p].ip_chunk;
+      q.ready = true;
+    }
     return NUASM_OK;
   };
   auto generations = [&] {
@@ -2140,6 +2158,8 @@ static nuasm_status batch_launch(nuasm_batch_s* b, BatchGraph& g, const std::vec
   g.key = key;
   g.M = M;
   g.buffers = generations();
+  if (binds)
+    for (const nuasm_plan_s* pl : b->plans) g.bound.push_back({pl->ps[0].M, pl->ps[0].sp_chunk, pl->ps[0].ip_chunk});
   ++b->recorded;
   return launch();
 }
@@ -2234,7 +2254,7 @@ nuasm_status nuasm_batch_run(nuasm_batch b, const int64_t* M, const double* cons
     key.push_back(in[p]);
     key.push_back(out[p]);
   }
-  return batch_launch(b, b->g_run, key, Ms, [&](nuasm_plan_s* pl, int p) {
+  return batch_launch(b, b->g_run, true, key, Ms, [&](nuasm_plan_s* pl, int p) {
     nuasm_status s = nuasm_set_points(pl, M[p], x[p], y[p]);
     if (s != NUASM_OK) return s;
     return nuasm_execute(pl, in[p], out[p]);
@@ -2254,7 +2274,7 @@ nuasm_status nuasm_set_points_many(nuasm_batch b, const int64_t* M, const double
     key.push_back(x[p]);
     key.push_back(y[p]);
   }
-  return batch_launch(b, b->g_bin, key, Ms,
+  return batch_launch(b, b->g_bin, true, key, Ms,
                       [&](nuasm_plan_s* pl, int p) { return nuasm_set_points(pl, M[p], x[p], y[p]); });
 }
 
@@ -2273,7 +2293,7 @@ nuasm_status nuasm_execute_many(nuasm_batch b, const void* const* in, void* cons
     key.push_back(in[p]);
     key.push_back(out[p]);
   }
-  return batch_launch(b, b->g_exec, key, Ms, [&](nuasm_plan_s* pl, int p) { return nuasm_execute(pl, in[p], out[p]); });
+  return batch_launch(b, b->g_exec, false, key, Ms, [&](nuasm_plan_s* pl, int p) { return nuasm_execute(pl, in[p], out[p]); });
 }
 
 namespace {
