@@ -125,15 +125,11 @@ __device__ __forceinline__ bool in_band(int k, int lo, int hi) { return k >= lo 
 // the band, a run of consecutive strips, sat on a few of the eight XCDs:
 // N' = 2048 with half the columns in band 36.6 us, N' = 8192 with 2020 in
 // band 284 us, one launch.)
-// (An explicit band that is empty along y alone may reach outside the n
-// columns along x: both ends are clamped to them.)
-__host__ __device__ __forceinline__ int band_strip0(const GridGeom& g, int n, int C) {
-  const int a = g.kxlo + n / 2;
-  return (a < 0 ? 0 : a) / C;
-}
+// (The n columns hold the band: K'' is chosen to, and a band empty along
+// either axis comes here empty along x, with no strip.)
+__host__ __device__ __forceinline__ int band_strip0(const GridGeom& g, int n, int C) { return (g.kxlo + n / 2) / C; }
 static int band_strips(const GridGeom& g, int n, int C) {
-  const int a0 = std::max(g.kxlo + n / 2, 0), a1 = std::min(g.kxhi + n / 2, n - 1);
-  return a0 > a1 ? 0 : a1 / C - a0 / C + 1;
+  return g.kxlo > g.kxhi ? 0 : (g.kxhi + n / 2) / C - band_strip0(g, n, C) + 1;
 }
 
 // float64 square root from the hardware seed (v_rsq_f64) refined by Newton
@@ -502,7 +498,6 @@ __device__ __forceinline__ void t2_cols_body(const ColArgs& a, int bid, int nbid
   float2* tw = s + Cfg::DATA;
   const int a0 = (band_strip0(g, NP, C) + xcd_remap(bid, nbid)) * C;
   const int kx0 = a0 - NP / 2;
-  if (kx0 < -N / 2 || kx0 >= N / 2) return;  // outside K'' (a band empty along y): no column of V
   const int tid = (int)threadIdx.x, c = tid % C, i0 = tid / C, kx = kx0 + c;
   const bool inx = in_band(kx, g.kxlo, g.kxhi);
   const int Nin = HALFIN ? NP / 2 : NP;

@@ -937,6 +937,19 @@ nuasm_status bind_grid(nuasm_plan_s* pl, PointSet& q, int64_t nx, int64_t ny, do
   return NUASM_OK;
 }
 
+// The plan's geometry as the grid passes take it.  A band that is empty along
+// y alone has no mode, and N'' is then as small as it gets, whatever the
+// extent along x: it is given to them empty along x too, so that no pass reads
+// columns that no column workgroup wrote.
+GridGeom pass_geom(const nuasm_plan_s* pl) {
+  GridGeom g = pl->geom;
+  if (g.kylo > g.kyhi) {
+    g.kxlo = 1;
+    g.kxhi = 0;
+  }
+  return g;
+}
+
 // Spreading of one point set's values onto the fine support (gridA).
 nuasm_status run_spread(nuasm_plan_s* pl, PointSet& q, const float2* vals) {
   hipStream_t st = pl->stream;
@@ -1022,7 +1035,7 @@ nuasm_status run_type1_pipeline(nuasm_plan_s* pl, PointSet& q, const float2* val
   hipStream_t st = pl->stream;
   nuasm_status s = run_spread(pl, q, vals);
   if (s != NUASM_OK) return s;
-  GridGeom g = pl->geom;
+  GridGeom g = pass_geom(pl);
   g.crop = crop ? 1 : 0;
   set_t1_strips(&g, pl->logNp);
   Spectral sp = pl->spec;
@@ -1046,7 +1059,7 @@ nuasm_status run_type1_pipeline(nuasm_plan_s* pl, PointSet& q, const float2* val
 nuasm_status run_type2_pipeline(nuasm_plan_s* pl, PointSet& q, const float2* plane, int Nin, float2* out,
                                 bool conj) {
   hipStream_t st = pl->stream;
-  GridGeom g = pl->geom;
+  GridGeom g = pass_geom(pl);
   g.Nin = Nin;
   g.crop = 0;
   set_t2_strips(&g, pl->logNpf, pl->logNp);
@@ -1076,7 +1089,7 @@ nuasm_status run_type3_pipeline(nuasm_plan_s* pl, PointSet& src, PointSet& dst, 
   hipStream_t st = pl->stream;
   nuasm_status s = run_spread(pl, src, vals);
   if (s != NUASM_OK) return s;
-  GridGeom g = pl->geom;
+  GridGeom g = pass_geom(pl);
   g.crop = 0;
   set_t3_strips(&g, pl->logNpf);
   Spectral sp = pl->spec;
