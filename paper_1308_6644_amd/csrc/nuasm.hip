@@ -678,10 +678,14 @@ void set_tile(nuasm_plan_s* pl, int tile) {
 // 64 x 64 bins and the register-gather spreading.
 constexpr int64_t kAutoChunks = 1024;
 
+bool chunks_follow_count(const nuasm_plan_s* pl) {
+  return !pl->ws && !stable_bins(pl) && pl->tile == kTile && pl->sp_method != 1;
+}
+
 void set_chunks(const nuasm_plan_s* pl, PointSet& q, int64_t M) {
   q.sp_chunk = pl->sp_chunk;
   q.ip_chunk = pl->ip_chunk;
-  if (pl->ws || stable_bins(pl) || pl->tile != kTile || pl->sp_method == 1) return;
+  if (!chunks_follow_count(pl)) return;
   auto fit = [](int64_t need, int64_t lo, int64_t hi) {
     return (int)std::min(hi, std::max(lo, (need + 255) / 256 * 256));
   };
@@ -755,9 +759,26 @@ int64_t scratch_tiles_needed(const nuasm_plan_s* pl, const PointSet& q) {
   return std::min<int64_t>(q.chunk_cap, (8 * q.M) / q.sp_chunk + 1);
 }
 
+// The most that any set within the record buffer's capacity may need.  With
+// chunk sizes that follow the count (set_chunks) the need does not grow with
+// it: up to 458752 points it comes near 2048 tiles again and again.
+int64_t scratch_tiles_most(const nuasm_plan_s* pl, const PointSet& q) {
+  const int64_t M = q.rec_cap;
+  int64_t t = (8 * M) / pl->sp_chunk + 1;
+  if (chunks_follow_count(pl) && pl->sp_auto)
+    t = std::max(t, M <= 8192 ? (8 * M) / (2 * kSpreadSubBatch) + 1
+                              : std::min<int64_t>((8 * M) / kSpreadSubBatch + 1, 2048));
+  return std::min(q.chunk_cap, t);
+}
+
+// Partial tiles for the bound set.  They are allocated for every set up to the
+// record buffer's capacity where only a bound of the need is known (16.8 MB
+// from 65504 points on, 8 KB a tile), and with a quarter to spare where the
+// count is exact, so that a new set of points seldom or never allocates.
 nuasm_status ensure_scratch(nuasm_plan_s* pl, PointSet& q) {
-  const int64_t need = std::max<int64_t>(scratch_tiles_needed(pl, q), 1);
+  int64_t need = std::max<int64_t>(scratch_tiles_needed(pl, q), 1);
   if (q.scratch && need <= q.scratch_chunks) return NUASM_OK;
+  need = std::max(need, q.synced ? std::min(need + need / 4, scratch_tiles_most(pl, q)) : scratch_tiles_most(pl, q));
   // a workspace holds the bound for its capacity, which covers every M <= it
   if (pl->ws) return fail(NUASM_ERR_INVALID_ARG, "split-bin scratch exceeds the workspace");
   if (q.scratch) {
@@ -880,6 +901,9 @@ nuasm_status bind_points(nuasm_plan_s* pl, PointSet& q, int64_t M, const double*
   q.exact_multi = q.host_stat[3];
   q.exact_slots = q.host_stat[5];
   q.synced = true;
+  // a plan that has spread before finds its partial tiles ready: its next
+  // execute allocates nothing (it may be under capture)
+  if (q.scratch && (s = ensure_scratch(pl, q)) != NUASM_OK) return s;
   q.ready = true;
   return NUASM_OK;
 }
