@@ -15,56 +15,62 @@ namespace nuasm {
 
 constexpr int kRsWaves = 8;   // waves per workgroup, each over an eighth of the sources
 constexpr int kRsBlock = 64;  // sources per float32 partial sum (then added in float64)
-constexpr double kRsNear = 1e5;  // largest |z|/l summed by the shorter form of the phase
 constexpr int kRsUnroll = 8;  // sources whose scalar loads are issued together
 
-// One pair's term of the sum, w (z/r)(1 - i k r) exp(i k r)/r^2 with
-// r = sqrt(rho^2 + z^2), divided by k z/z^2 (the caller multiplies the sum).
-// (dx, dy) is the pair's distance over |z| and s = r/|z| = sqrt(u),
-// u = 1 + dx^2 + dy^2.
+// One pair's term of the sum, w (z/r)(1 - i k r) exp(i k r)/r^2, up to the
+// factor that the caller multiplies the sum by.  Lengths are in units of 1/p, p
+// the power of two that brings |z| into [1/2, 1) as zs (scaling by it is
+// exact): (dx, dy) is the pair's distance, R = sqrt(zs^2 + dx^2 + dy^2).
+// Either way the phase is |z|/l, reduced to c0 on the host, plus the path
+// difference (r - |z|)/l, which is formed in float64 without cancellation and
+// reduced by whole cycles before the float32 sine and cosine.
 //
-// FAR = false, |z|/l <= kRsNear: the phase k r / (2 pi) = (|z|/l) s is formed
-// in float64 and reduced by whole cycles before the float32 sine and cosine.
-// s comes from the float32 estimate y0 of 1/sqrt(u) (relative error d <= 1e-7)
-// by one residual correction, s0 = u y0, s = s0 + (u - s0^2) y0/2, whose error
-// is 1.5 d^2 <= 1.4e-14 (1.3e-15 rms): 1.4e-9 cycles at |z|/l = 1e5, a twentieth
-// of the float32 argument's own rounding.  The product with |z|/l is reduced by
-// a fused multiply-add and rounds once.
-// FAR = true: that product would keep too few digits, so (r - |z|)/l is formed
-// without cancellation as rho^2 / (l |z| (1 + s)), 1/(1 + s) from the float32
-// estimate by one Newton step, and |z|/l enters as its fraction c0.
+// FAR = false, |z|/l <= kRsNear: with y0, the float32 estimate of 1/R (relative
+// error d, at most 2e-7), R2 y0 - zs is the path difference D up to d R, the
+// residual e = rho^2 - D (D + 2 zs) holds the rest to the last digit, and
+// h = e y0 / 2 corrects it to 1.5 d^2 R, which the float32 term 1.5 h^2 y0 takes
+// to d^3 R.  Error: a few 2^-53 of the path difference and 3e-20 |z|/l; emulated
+// on the CPU, |z|/l from 20 to 1e5 and windows of 0.1 mm to 4 m: 2e-16 of the
+// path difference at most, where the FAR form has 3e-14.
+// FAR = true, in units of |z|: D = rho^2 / (1 + s), s = R = sqrt(1 + rho^2), from
+// the estimates of 1/s and of 1/(1 + s) by a Newton step each (1e-14 of D).  It
+// stays below the d^3 term where |z|/l is large and the path difference small
+// (|z|/l = 2e8, a window of 1 mm: 2e-16 cycles, and 6e-12 by the other).
 //
-// The amplitude needs float32 only.  With y = 1/s (corrected: the estimate's
-// error is (u - s0^2) y0^2 / 2), z/r^3 = a3 y^3 and k z/r^2 = ak y^2, the term is
-// ak y^2 ((a3/ak) y - i) (w e).
-// 35 issue slots a pair where the FAR form alone took 43 (an instruction each,
-// two a transcendental): 65536 x 65536 pairs 4.66 -> 3.86 ms
-// (1.11e12 pairs/s, 90 % of vector issue).
+// The amplitude needs float32 only.  With y = 1/R (its square corrected by h),
+// z/r^3 = a3 y^3 and k z/r^2 = ak y^2, the term is ak y^2 ((a3/ak) y - i) (w e).
+// 65536 x 65536 pairs: 4.66 ms with the FAR form and the amplitude as separate
+// products, 3.83 with (|z|/l) s in the place of the path difference, whose error
+// is 1e-14 of |z|/l (1e-9 cycles at 1e5), 4.14 so (1.04e12 pairs/s).
 template <bool FAR>
 __device__ __forceinline__ void rs_add(double dx, double dy, float2 w, const RsConst& k, float& sr, float& si) {
   const double rho2 = fma(dx, dx, dy * dy);
-  const double u = FAR ? 1.0 + rho2 : fma(dx, dx, fma(dy, dy, 1.0));
-  const float y0f = __builtin_amdgcn_rsqf((float)u);
-  const double y0 = (double)y0f;
-  double cyc;
-  float yf;
+  float cycf, y, y2;  // y: 1/R, and its square
   if constexpr (FAR) {
-    const double y = y0 * fma(-0.5 * u, y0 * y0, 1.5);
-    const double d = fma(u, y, 1.0);
+    const double u = fma(rho2, k.inv_zs2, 1.0);
+    double v = (double)__builtin_amdgcn_rsqf((float)u);
+    v = v * fma(-0.5 * u, v * v, 1.5);
+    const double d = fma(u, v, 1.0);
     double q = (double)__builtin_amdgcn_rcpf((float)d);
     q = q * fma(-d, q, 2.0);
-    cyc = fma(rho2 * k.zl, q, k.c0);
-    cyc -= rint(cyc);
-    yf = (float)y;
+    const double cyc = fma(rho2 * k.inv_lz, q, k.c0);
+    cycf = (float)(cyc - rint(cyc));
+    y = (float)v;
+    y2 = y * y;
   } else {
-    const double s0 = u * y0;
-    const double eh = fma(-s0, s0, u) * (0.5 * y0);
-    const double s = s0 + eh;
-    cyc = fma(k.zl, s, -rint(k.zl * s));
-    yf = fmaf((float)eh, y0f * y0f, y0f);
+    const double R2 = rho2 + k.zs2;
+    y = __builtin_amdgcn_rsqf((float)R2);
+    const double y0 = (double)y;
+    const double D0 = fma(R2, y0, -k.zs);
+    const double h2 = fma(-D0, D0 + k.two_zs, rho2) * y0;  // 2 h
+    const double cyc = fma(fma(0.5, h2, D0), k.inv_l, k.c0);
+    const float h2f = (float)h2, t = h2f * y;
+    cycf = fmaf(k.corr * h2f, t, (float)(cyc - rint(cyc)));
+    y2 = y * y;
+    y2 = fmaf(t, y2, y2);
   }
-  const float2 e = cis_rev((float)cyc);
-  const float y2 = yf * yf, b = k.ratio * yf;
+  const float2 e = cis_rev(cycf);
+  const float b = k.ratio * y;
   // P = w e; P (b - i) = (P.x b + P.y, P.y b - P.x)
   const float pr = fmaf(w.x, e.x, -(w.y * e.y)), pi = fmaf(w.x, e.y, w.y * e.x);
   sr = fmaf(fmaf(pr, b, pi), y2, sr);
@@ -81,15 +87,15 @@ k_rs_direct(const double* __restrict__ x1, const double* __restrict__ y1, const 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t j = (int64_t)blockIdx.x * 64 + lane;
   const bool live = j < M2;
-  const double X = ((live ? x2[j] : 0.0) + k.ox) * k.inv_az;
-  const double Y = ((live ? y2[j] : 0.0) + k.oy) * k.inv_az;
+  const double X = ((live ? x2[j] : 0.0) + k.ox) * k.p;
+  const double Y = ((live ? y2[j] : 0.0) + k.oy) * k.p;
   const int64_t per = (M1 + kRsWaves - 1) / kRsWaves;
   const int64_t i0 = min(M1, (int64_t)wave * per);
   const int64_t i1 = min(M1, i0 + per);
   double accr = 0.0, acci = 0.0;
   float sr = 0.f, si = 0.f;
   auto pair = [&](double sx, double sy, float2 w) {
-    rs_add<FAR>(fma(-sx, k.inv_az, X), fma(-sy, k.inv_az, Y), w, k, sr, si);
+    rs_add<FAR>(fma(-sx, k.p, X), fma(-sy, k.p, Y), w, k, sr, si);
   };
   int64_t i = i0;
   // full groups of kRsUnroll sources: their scalar loads are issued together
@@ -134,7 +140,7 @@ hipError_t launch_rs_direct(const double* x1, const double* y1, const float2* c,
                             const double* y2, int64_t M2, const RsConst& k, float2* out, hipStream_t st) {
   if (M2 <= 0) return hipSuccess;
   const int64_t grid = (M2 + 63) / 64;
-  if (k.zl <= kRsNear)
+  if (!k.far)
     hipLaunchKernelGGL(k_rs_direct<false>, dim3((unsigned)grid), dim3(64 * kRsWaves), 0, st, x1, y1, c, M1, x2, y2,
                        M2, k, out);
   else

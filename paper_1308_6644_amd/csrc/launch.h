@@ -243,13 +243,19 @@ hipError_t launch_t3_cols(int logNp, const float2* T, float2* V, GridGeom g, Spe
                           const float2* tw, hipStream_t st);
 
 // Rayleigh-Sommerfeld direct summation (Eq. 10): constants of one propagation
+constexpr double kRsNear = 1e5;  // largest |z|/l summed by the shorter form of the phase
 struct RsConst {
   double ox, oy;     // offset o added to the destination points, metres
-  double inv_az;     // 1 / |z|
-  double zl;         // |z| / l
-  double c0;         // the same reduced to [-1/2, 1/2]
-  double scale;      // ak / (2 pi): k z / (2 pi z^2), k = 2 pi / l
-  float ratio;       // a3 / ak = (z / |z|^3) / (k z / z^2) = 1 / (k |z|)
+  double p;          // power of two with zs = p |z| in [1/2, 1)
+  double zs, two_zs, zs2;
+  double inv_l;      // 1 / (p l)
+  double inv_zs2;    // 1 / zs^2
+  double inv_lz;     // 1 / (p l zs)
+  double c0;         // |z| / l reduced to [-1/2, 1/2]
+  double scale;      // ak / (2 pi): k z / (2 pi r^2) at y = 1, k = 2 pi / l
+  float corr;        // 3/8 of inv_l
+  float ratio;       // a3 / ak: 1 / (k r) at y = 1
+  bool far;          // |z| / l > kRsNear
 };
 hipError_t launch_rs_direct(const double* x1, const double* y1, const float2* c, int64_t M1, const double* x2,
                             const double* y2, int64_t M2, const RsConst& k, float2* out, hipStream_t st);

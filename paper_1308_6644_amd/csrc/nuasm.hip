@@ -1776,11 +1776,22 @@ nuasm_status nuasm_rs_direct(int64_t M1, const double* x1, const double* y1, con
   RsConst kc{};
   kc.ox = ox;
   kc.oy = oy;
-  kc.inv_az = 1.0 / az;
-  kc.zl = zl;
+  int e = 0;
+  (void)std::frexp(az, &e);
+  kc.p = std::ldexp(1.0, std::min(1000, std::max(-1000, -e)));
+  kc.zs = az * kc.p;
+  kc.two_zs = 2.0 * kc.zs;
+  kc.zs2 = kc.zs * kc.zs;
+  kc.inv_l = 1.0 / (kc.p * lambda);
+  kc.inv_zs2 = 1.0 / kc.zs2;
+  kc.inv_lz = 1.0 / (kc.p * lambda * kc.zs);
   kc.c0 = zl - std::nearbyint(zl);
-  kc.scale = k * z / (z * z) / (2.0 * kPi);
-  kc.ratio = (float)(1.0 / (k * az));
+  kc.corr = (float)(0.375 * kc.inv_l);
+  // the amplitude's y: |z| / r in the far form, 1 / (p r) in the other
+  kc.far = !(zl <= kRsNear);
+  const double yz = kc.far ? 1.0 : 1.0 / kc.zs;  // y at r = |z|
+  kc.scale = k * z / (z * z) / (2.0 * kPi) / (yz * yz);
+  kc.ratio = (float)(1.0 / (k * az * yz));
   HIP_TRY(launch_rs_direct(x1, y1, (const float2*)c, M1, x2, y2, M2, kc, (float2*)out, (hipStream_t)stream),
           "launch rs_direct");
   return NUASM_OK;
