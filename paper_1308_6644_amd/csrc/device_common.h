@@ -78,9 +78,10 @@ __device__ __forceinline__ void bfly_i(float2& a, float2& b) {
 // operations each: 72 for R = 8 and 16 for the powers, where separate products
 // by w .. w^7 and a plain transform took 84 and 24.
 // PH: the pass has no twiddles of its own (w = exp(DIR 2 pi i PH / 16), PH = 0,
-// or 1 for the half-shifted first pass of radix 8); else w is given.
+// or 1 for the half-shifted first pass of radix 8); else w is given, and w4 = w^4
+// for radix 8.
 template <int R, int DIR, int PH>
-__device__ __forceinline__ void dft_tw(float2 (&x)[R], float2 w) {
+__device__ __forceinline__ void dft_tw(float2 (&x)[R], float2 w, float2 w4) {
   if constexpr (R == 2) {
     bfly(x[0], x[1], w);
   } else if constexpr (R == 4) {
@@ -112,7 +113,7 @@ __device__ __forceinline__ void dft_tw(float2 (&x)[R], float2 w) {
       bfly_i<DIR>(x[2], x[3]);
       bfly(x[6], x[7], rot16<DIR>(6, one));
     } else {
-      float2 w1 = w, w2, w4;
+      float2 w1 = w, w2;
       if constexpr (PH > 0) {
         w1 = rot16<DIR>(PH, one);
         w2 = rot16<DIR>(2 * PH, one);
@@ -123,7 +124,6 @@ __device__ __forceinline__ void dft_tw(float2 (&x)[R], float2 w) {
         static_assert(PH <= 1, "w^4 is a quarter turn");
       } else {
         w2 = cmul(w, w);
-        w4 = cmul(w2, w2);
         bfly(x[0], x[4], w4);
         bfly(x[2], x[6], w4);
         bfly(x[1], x[5], w4);
@@ -202,6 +202,18 @@ __device__ __forceinline__ float2 tw2_get(const float2* __restrict__ t, int m) {
 // may still be in use by other threads when a transform begins (its first
 // pass waits before it writes); nothing is left in LDS at the end, but other
 // threads may still be reading.
+// Largest LOGN whose w^4 is a table value too, and not the square of a square
+// (five roundings, at four times the first one's weight).  Error of
+// transforms of twice the length on random data, with squares and so: 256
+// 1.31e-7 and 1.11e-7, 1024 2.55e-7 and 1.74e-7, 2048 2.67e-7 and 1.81e-7; of a
+// plane with few modes (N = 256, Fresnel, z = 0.43 m), whose errors add up
+// rather than average out, 9.1e-7 and 7.6e-7 (8.4e-7 with full-length
+// transforms and the twiddles as separate factors).  The same number of
+// products and one or two LDS reads more: no difference in time up to 2^10
+// (N' = 2048, Fresnel type 2 of 2^20 points 112.1 and 111.5 us), 1 % at 2^11 and
+// beyond (114.5 and 116), where squares already err less than those factors did.
+constexpr int kTableW4 = 10;
+
 template <int LOGN, int C, int NT, int DIR, bool HALF, int TL, int P, int REM>
 __device__ __forceinline__ void reg_fft_pass(float2* __restrict__ s, const float2* __restrict__ tw, int tid,
                                              float2 (&x)[8]) {
@@ -223,7 +235,7 @@ __device__ __forceinline__ void reg_fft_pass(float2* __restrict__ s, const float
       if constexpr (FIRST) {
 #pragma unroll
         for (int j = 0; j < R; ++j) y[j] = x[j];
-        dft_tw<R, DIR, HALF ? 1 : 0>(y, czero());
+        dft_tw<R, DIR, HALF ? 1 : 0>(y, czero(), czero());
       } else {
         if constexpr ((NR * C) % 16 == 0) {
           // inputs NR * C elements apart: one padded address and constant
@@ -239,7 +251,15 @@ __device__ __forceinline__ void reg_fft_pass(float2* __restrict__ s, const float
         const int idx = TL > LOGN ? ((2 * k + (HALF ? 1 : 0)) * TWS) << (TL > LOGN ? TL - LOGN - 1 : 0) : k * TWS;
         float2 w = tw2_get<TL>(tw, idx);
         if (DIR > 0) w.y = -w.y;
-        dft_tw<R, DIR, -1>(y, w);
+        float2 w4 = czero();
+        if constexpr (R == 8 && LOGN <= kTableW4) {
+          w4 = tw2_get<TL>(tw, (4 * idx) & ((1 << TL) - 1));
+          if (DIR > 0) w4.y = -w4.y;
+        } else if constexpr (R == 8) {
+          w4 = cmul(w, w);
+          w4 = cmul(w4, w4);
+        }
+        dft_tw<R, DIR, -1>(y, w, w4);
       }
       // register j * PER + q: in the last pass that is element i0 + m N / 8,
       // m = q + j 8 / R
