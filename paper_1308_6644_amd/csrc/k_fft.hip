@@ -84,7 +84,15 @@ constexpr int imax(int a, int b) { return a > b ? a : b; }
 
 // Longest transform of the three column passes (their strip widths follow).
 constexpr int t1_cols_log(int lpf, int lp) { return imax(lpf, lp); }
-constexpr int t2_cols_log(int lpf, int lp, bool halfin) { return halfin && lpf < lp ? imax(lpf, lp - 1) : lp; }
+// Whether the type-2 column pass runs its forward transform by half-length
+// ones.  That takes half the LDS and one dependent transform more: it pays where
+// a whole column fills a workgroup's LDS.  t2_cols and the row pass that reads
+// its strips, split and whole, us a launch: N' = 512, N'' = 256 12.6 + 7.6 and
+// 9.9 + 7.2 (full-length transforms throughout: 11.8 + 7.2), N' = 2048, N'' = 1024
+// 18.7 + 14.7 and 17.0 + 14.7, N' = 4096, N'' = 2048 40.5 + 20.7 and 38.2 + 25.6,
+// N' = 8192, N'' = 4096 140 + 86 and 163 + 86.
+constexpr bool t2_split(int lpf, int lp, bool halfin) { return halfin && lpf < lp && lp >= 12; }
+constexpr int t2_cols_log(int lpf, int lp, bool halfin) { return t2_split(lpf, lp, halfin) ? imax(lpf, lp - 1) : lp; }
 // Strip widths of the arrays a column pass reads (cs) and writes (cv), whole
 // multiples of its C columns.  A strip wider than C costs the column pass
 // partial requests and saves them in the row pass: four columns balance the
@@ -482,8 +490,8 @@ __device__ __forceinline__ void store_support_rows(float2* __restrict__ strip, i
 // of Eq. 4) times H(k) Rect(k) (-1)^k_y / psihat(k_y) / N'^2 -> inverse
 // nf-point FFT along y (nf = 2 N'') -> the support rows [s0, s0 + L), N''
 // columns k_x + N''/2.  HALFIN: Nin = N.  With a narrow band (N'' < N') the
-// forward transform of a half-empty column runs by half-length transforms and
-// its modes reach the inverse one through LDS; otherwise it runs at full
+// modes of the forward transform, at full length or by half-length transforms
+// (t2_split), reach the inverse one through LDS; otherwise it runs at full
 // length, which leaves every mode in the register where the inverse
 // transforms want it.
 template <int LPF, int LP, bool HALFIN>
@@ -491,7 +499,7 @@ __device__ __forceinline__ void t2_cols_body(const ColArgs& a, int bid, int nbid
   const GridGeom& g = a.g;
   const Spectral& sp = a.sp;
   constexpr int N = 1 << LPF, NP = 1 << LP, TL = imax(LPF + 1, LP);
-  constexpr bool SPLIT = HALFIN && LPF < LP;
+  constexpr bool SPLIT = t2_split(LPF, LP, HALFIN);
   using Cfg = ColCfg<t2_cols_log(LPF, LP, HALFIN), TL>;
   constexpr int C = Cfg::C, NT = Cfg::NT, NA = C * N / 8;
   extern __shared__ float2 s[];
