@@ -1334,11 +1334,15 @@ __device__ __forceinline__ void spread_reduce_body(const SpreadReduceArgs& a, in
 // and with it, 1943215 points on 528 x 528 cells: w = 7 49.4 and 35.8 us, 6
 // 38.8 and 33.4, 5 32.5 and 33.2, 4 30.0 and about 34; 2^20 clustered on
 // 2064 x 2064: 32.2 and 28.7, 26.9 and 27.3, 25.1 and 26.3).  Nor is anything
-// sorted in a launch of fewer than kInterpSortChunks chunks, five for four CUs:
-// with a workgroup or so to a CU the LDS keeps up, and the sort is latency on
-// its longest chunk (w = 7, clustered, without and with: 60000 points at N = 64
-// 7.4 and 8.3 us, 500000 at N = 256 19.4 and 20.8, 10^6 29.0 and 24.6).  Same
-// sums either way, in the same order.
+// sorted in a point set of fewer than kInterpSortChunks chunks, five for four
+// CUs: with a workgroup or so to a CU the LDS keeps up, and the sort is latency
+// on its longest chunk (w = 7, clustered, without and with: 60000 points at
+// N = 64 7.4 and 8.3 us, 500000 at N = 256 19.4 and 20.8, 10^6 29.0 and 24.6).
+// That is each plane's own count in a batch too, where more workgroups are in
+// flight: sorted by the count of a whole grouped launch, 16 planes of N = 256 to
+// 1024 take as long (466.7 us a run, and 466.6 so), and of N up to 512 no less
+// (288.8, and 287.6 so), since the other chain's launches fill what the LDS
+// leaves idle.  Same sums either way, in the same order.
 // w = 7: 2^24 points (4 a cell) 356 -> 301 us, 2^22 in three clusters 108 ->
 // 99, 2^20 clustered 32.2 -> 27.5.  At 2^24 points the 8-byte stores in caller
 // order (a 64-byte write each between the L2s and the Infinity Cache) are the
@@ -1347,7 +1351,7 @@ constexpr int kInterpThreads = 256;
 constexpr int kInterpBatch = 4;
 constexpr int kInterpSortMin = 384;  // records from which a batch is sorted
 constexpr int kInterpSortTaps = 6;   // and taps an axis
-constexpr int kInterpSortChunks = 320;  // and chunks of the launch
+constexpr int kInterpSortChunks = 320;  // and chunks of the point set
 // (launch bound: at least 5 waves per SIMD, i.e. at most 96 VGPRs)
 
 template <int W, int TILE>
