@@ -138,8 +138,10 @@ typedef struct {
   int64_t M;                  /* points of the last set_points (0 if none) */
   size_t device_bytes;        /* device memory the plan holds */
   int64_t M_dest;             /* type 3: points of the last set_dest_points */
-  int32_t spread_chunk;       /* records per spreading workgroup (tuning) */
-  int32_t interp_chunk;       /* records per interpolation workgroup (tuning) */
+  int32_t spread_chunk;       /* max records per spreading workgroup and per */
+  int32_t interp_chunk;       /* interpolation workgroup, of the bound points (type
+                                 3: sources and destinations); before any are
+                                 bound, the largest that a set may get (tuning) */
   int32_t bin_range_points;   /* points per binning workgroup for M (tuning) */
   int32_t Npf;                /* spectral grid N'': N', or, when the band of Eq. 4
                                  is narrow, the smallest power of two >= max(32,
@@ -149,11 +151,18 @@ typedef struct {
 
 /* Launch-shape tuning of a plan (see nuasm_plan_set_tuning); 0 = default. */
 typedef struct {
-  int32_t spread_chunk;       /* max records per spreading workgroup: 0 = 1792;
-                                 a value below 1792 selects the small size
-                                 (896 records for w <= 8, 1024 above) */
-  int32_t interp_chunk;       /* max records per interpolation workgroup: 0 = 2048,
-                                 else 256 .. 65536 */
+  int32_t spread_chunk;       /* max records per spreading workgroup: 0 = automatic:
+                                 256 .. 1792, a multiple of 256 that follows the
+                                 point count so that 8 M / spread_chunk stays
+                                 below 2048 (512 up to 8192 points); 1792 from
+                                 458 000 points on, on a caller's workspace, in
+                                 deterministic mode, with bin_tile 64 and with
+                                 the register gather.  A value below 1792 selects
+                                 the small size (896 records for w <= 8, 1024
+                                 above), any other 1792 */
+  int32_t interp_chunk;       /* max records per interpolation workgroup: 0 =
+                                 automatic: 512 .. 2048 likewise, at most 1024
+                                 workgroups below 2048; else 256 .. 65536 */
   int32_t bin_range_points;   /* points per binning workgroup: 0 = automatic
                                  (max(4096, M/256), at most 65535), else 1024 .. 65535 */
   int32_t spread_method;      /* 0 = automatic (matrix cores), 1 = register gather
@@ -284,7 +293,8 @@ nuasm_status nuasm_execute(nuasm_plan plan, const void* in_dev, void* out_dev);
  * it.  Returns NUASM_ERR_UNSUPPORTED, enqueuing nothing, if the bound points
  * may need more tiles than the array holds (the exact need is known when
  * set_points synchronised; with NUASM_DEFER_RANGE_CHECK a bound of
- * 8 M / spread_chunk tiles is used), and the errors of nuasm_execute. */
+ * 8 M / nuasm_plan_info.spread_chunk + 1 tiles is used), and the errors of
+ * nuasm_execute. */
 nuasm_status nuasm_execute_noalloc(nuasm_plan plan, const void* in_dev, void* out_dev);
 
 /* Apply the adjoint (conjugate transpose) of the plan's operator, derived

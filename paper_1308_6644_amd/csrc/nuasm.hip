@@ -1401,8 +1401,11 @@ nuasm_status nuasm_plan_get_info(nuasm_plan pl, nuasm_plan_info* info) {
   info->device_bytes = pl->bytes;
   info->M_dest = M2;
   info->Npf = pl->geom.Npf;
-  info->spread_chunk = pl->sp_chunk;
-  info->interp_chunk = pl->ip_chunk;
+  // of the bound points (type 3: spreading's sources, interpolation's
+  // destinations); before any are bound, the largest a set may get
+  const PointSet &src = pl->ps[0], &dst = pl->ps[pl->nsets - 1];
+  info->spread_chunk = src.ready && !src.grid ? src.sp_chunk : pl->sp_chunk;
+  info->interp_chunk = dst.ready && !dst.grid ? dst.ip_chunk : pl->ip_chunk;
   {
     int ppw = 0, G = 0;
     bin_ranges(M, pl->bin_ppw, stable_bins(pl), &ppw, &G);
