@@ -1730,6 +1730,13 @@ nuasm_status nuasm_debug_interp(nuasm_plan pl, int32_t which, const void* grid, 
   PointSet& q = pl->ps[which];
   if (!q.ready) return fail(NUASM_ERR_NOT_READY, "the point set is not bound");
   if (!out && q.M > 0) return fail(NUASM_ERR_INVALID_ARG, "out is NULL");
+  if ((uintptr_t)grid & 15) {
+    // the kernel reads pairs of cells; the plan's own grids are aligned for it
+    HIP_TRY(hipMemcpyAsync(pl->gridB, grid, sizeof(float2) * (size_t)pl->geom.L * pl->geom.L,
+                           hipMemcpyDeviceToDevice, pl->stream),
+            "hipMemcpyAsync");
+    grid = pl->gridB;
+  }
   return run_interp(pl, q, (const float2*)grid, (float2*)out);
 }
 
