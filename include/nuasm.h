@@ -259,11 +259,10 @@ nuasm_status nuasm_set_dest_points(nuasm_plan plan, int64_t M, const double* x_d
  * the point-side arrays of execute / execute_adjoint are [ny][nx] in that
  * order.  The whole grid must lie in the window [-N g/2, N g/2]^2
  * (NUASM_ERR_OUT_OF_RANGE otherwise, checked on the host, nothing enqueued).
- * Such a set needs no binning: spreading and interpolation run as two
- * separable 1-D passes each (the stage timers record two launches under
- * NUASM_STAGE_SPREAD / NUASM_STAGE_INTERP).  May allocate a workspace of
- * max(rows reached x nx, ny x L) complex values; never synchronises
- * otherwise.  nx, ny <= 2^18, nx ny <= 2^30. */
+ * Such a set needs no binning: spreading runs as two separable 1-D passes
+ * (NUASM_STAGE_SPREAD times them together), interpolation as one launch of
+ * both.  May allocate a workspace of ny x L complex values for the spreading
+ * (not for a NUASM_FORWARD_ONLY plan); never synchronises otherwise.  nx, ny <= 2^18, nx ny <= 2^30. */
 nuasm_status nuasm_set_grid_points(nuasm_plan plan, int32_t which, int64_t nx, int64_t ny, double pitch, double cx,
                                    double cy);
 

@@ -908,6 +908,24 @@ nuasm_status bind_points(nuasm_plan_s* pl, PointSet& q, int64_t M, const double*
   return NUASM_OK;
 }
 
+// The rows of a bound grid spread along x, before the pass along y: what
+// spreading from a grid needs, and interpolation does not.
+nuasm_status ensure_grid_rows(nuasm_plan_s* pl, PointSet& q) {
+  const int64_t need = q.gp.ny * (int64_t)q.gp.L;
+  if (need <= q.gbuf_cap) return NUASM_OK;
+  HIP_TRY(hipStreamSynchronize(pl->stream), "hipStreamSynchronize");
+  if (q.gbuf) {
+    ++pl->buffers;
+    (void)dev_free(q.gbuf);
+    pl->bytes -= sizeof(float2) * q.gbuf_cap;
+    q.gbuf = nullptr;
+    q.gbuf_cap = 0;
+  }
+  HIP_TRY(dalloc(pl, &q.gbuf, (size_t)need), "hipMalloc(grid passes)");
+  q.gbuf_cap = need;
+  return NUASM_OK;
+}
+
 // Bind a uniform nx x ny grid of the given pitch centred at (cx, cy) as a
 // point set: no device work, the separable kernels derive every tap from the
 // grid index.  Host-side range check of the grid's extreme points.
@@ -940,19 +958,9 @@ nuasm_status bind_grid(nuasm_plan_s* pl, PointSet& q, int64_t nx, int64_t ny, do
   p.L = pl->geom.L;
   p.two_over_w = 2.0f / (float)pl->w;
   p.beta_log2e = pl->beta * 1.4426950408889634f;
-  // rows spread along x, before the pass along y
-  const int64_t need = ny * (int64_t)p.L;
-  if (need > q.gbuf_cap) {
-    HIP_TRY(hipStreamSynchronize(pl->stream), "hipStreamSynchronize");
-    if (q.gbuf) {
-      ++pl->buffers;
-      (void)dev_free(q.gbuf);
-      pl->bytes -= sizeof(float2) * q.gbuf_cap;
-      q.gbuf = nullptr;
-      q.gbuf_cap = 0;
-    }
-    HIP_TRY(dalloc(pl, &q.gbuf, (size_t)need), "hipMalloc(grid passes)");
-    q.gbuf_cap = need;
+  if (!(pl->p.flags & NUASM_FORWARD_ONLY)) {
+    const nuasm_status s = ensure_grid_rows(pl, q);
+    if (s != NUASM_OK) return s;
   }
   q.grid = true;
   q.M = nx * ny;
@@ -978,6 +986,9 @@ GridGeom pass_geom(const nuasm_plan_s* pl) {
 nuasm_status run_spread(nuasm_plan_s* pl, PointSet& q, const float2* vals) {
   hipStream_t st = pl->stream;
   if (q.grid) {
+    // (already there, but for a forward-only plan's nuasm_debug_spread)
+    const nuasm_status s = ensure_grid_rows(pl, q);
+    if (s != NUASM_OK) return s;
     StageScope sc(pl, NUASM_STAGE_SPREAD);
     HIP_TRY(launch_grid_spread(pl->w, vals, q.gbuf, pl->gridA, q.gp, st), "launch grid_spread");
     return NUASM_OK;
