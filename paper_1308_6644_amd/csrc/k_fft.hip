@@ -113,15 +113,10 @@ __device__ __forceinline__ size_t strip_at(int rows, int cs, int row, int col) {
   return (((size_t)(col >> cs) * rows + row) << cs) + (col & ((1 << cs) - 1));
 }
 
-// Columns col (even) and col + 1 of a row; cs is 0 only for the longest columns.
+// Columns col (even) and col + 1 of a row (cs is 2 at least).
 __device__ __forceinline__ void strip_store2(float2* __restrict__ a, int rows, int cs, int row, int col, float2 v0,
                                              float2 v1) {
-  if (cs > 0) {
-    *reinterpret_cast<float4*>(a + strip_at(rows, cs, row, col)) = make_float4(v0.x, v0.y, v1.x, v1.y);
-  } else {
-    a[strip_at(rows, cs, row, col)] = v0;
-    a[strip_at(rows, cs, row, col + 1)] = v1;
-  }
+  *reinterpret_cast<float4*>(a + strip_at(rows, cs, row, col)) = make_float4(v0.x, v0.y, v1.x, v1.y);
 }
 
 __device__ __forceinline__ bool in_band(int k, int lo, int hi) { return k >= lo && k <= hi; }
