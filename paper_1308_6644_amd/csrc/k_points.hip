@@ -459,10 +459,12 @@ __device__ __forceinline__ void bin_scatter_body(const BinArgs& a, int bid, int)
 // each scan the bin totals themselves (17 KB at T = 4225, out of L2), so that
 // no launch is needed between the column scan and the scatter; one more
 // workgroup per 1024 bins, dispatched first, writes the bin bases and the
-// chunk tables that the later kernels read.  Taken up to the bin count whose cursors fit the
-// scatter's LDS.  2^20 points, 4225 bins: column scan + bin scan + scatter
-// 7.3 + 4.7 + 16.9 us, now column scan + scatter 5.3 + 19.4 us and one gap
-// between launches less.
+// chunk tables that the later kernels read.  Taken where a thread scans at most
+// eight totals: up to 4225 bins, the next count being 16641.  2^20 points, 4225
+// bins: column scan + bin scan + scatter 7.3 + 4.7 + 16.9 us, now column scan +
+// scatter 5.3 + 19.4 us and one gap between launches less.
+
+constexpr int kScanPerThread = 8;  // totals a thread scans, entry T included
 
 __host__ __device__ constexpr int bin_table_workgroups(int T) { return (T + kBinThreads - 1) / kBinThreads; }
 
@@ -473,7 +475,7 @@ __host__ __device__ constexpr int bin_table_workgroups(int T) { return (T + kBin
 template <class Count, class Base>
 __device__ __forceinline__ void bin_tables(int T, const BinScanOut& so, int rejected, int u0, int u1,
                                            const Count& count, const Base& base) {
-  constexpr int NW = kBinThreads / 64, RMAX = kScatterCursorBytes / 4 / kBinThreads;
+  constexpr int NW = kBinThreads / 64, RMAX = kScanPerThread;
   __shared__ int part[kWgVals][RMAX * NW];
   const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int rounds = (T + kBinThreads - 1) / kBinThreads;
@@ -585,7 +587,7 @@ __device__ __forceinline__ void bin_scatter_scan_body(const BinScatterArgs& sa, 
   const int T = g.TX * g.TX;
   const int* __restrict__ total = sa.total;
   extern __shared__ unsigned sh[];
-  constexpr int NW = kBinThreads / 64, NB = 8;  // bins per thread and stage
+  constexpr int NW = kBinThreads / 64, NB = kScanPerThread;
   const int ntab = bin_table_workgroups(T);
   if (bid < ntab) {
     bin_tables(T, sa.so, total[T], bid, bid + 1, [&](int b) { return total[b]; }, [](int, int) {});
@@ -595,7 +597,7 @@ __device__ __forceinline__ void bin_scatter_scan_body(const BinScatterArgs& sa, 
   const double* __restrict__ x = a.x;
   const double* __restrict__ y = a.y;
   __shared__ int part[NB * NW];
-  static_assert(NB * NW == 128, "a stage's wave sums are scanned two per lane");
+  static_assert(NB * NW == 128, "the wave sums are scanned two per lane");
   const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int* myoff = a.off + (size_t)range * (T + 1);
   const int64_t j0 = (int64_t)range * a.ppw;
@@ -612,18 +614,17 @@ __device__ __forceinline__ void bin_scatter_scan_body(const BinScatterArgs& sa, 
     }
   };
   load(j0);  // the first batch in flight with the cursor staging
-  int carry = 0;
-  for (int b0 = 0; b0 <= T; b0 += kBinThreads * NB) {
-    // rounds of 1024 bins left, entry T included.  Inside a round every load
+  {
+    // rounds of 1024 bins, entry T included.  Inside a round every load
     // and LDS write is unconditional: a bin past T is clamped to T (whose
     // total counts for nothing here) and its cursor written, with the same
     // value, by several lanes
-    const int nu = (T - b0) / kBinThreads + 1;
+    const int nu = T / kBinThreads + 1;
     int v[NB], o[NB];
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
       if (u >= nu) break;
-      const int b = min(b0 + t + u * kBinThreads, T);
+      const int b = min(t + u * kBinThreads, T);
       v[u] = total[b];
       o[u] = myoff[b];
     }
@@ -632,7 +633,7 @@ __device__ __forceinline__ void bin_scatter_scan_body(const BinScatterArgs& sa, 
     for (int u = 0; u < NB; ++u) {
       int inc = 0;
       if (u < nu) {
-        if (b0 + t + u * kBinThreads >= T) v[u] = 0;
+        if (t + u * kBinThreads >= T) v[u] = 0;
         inc = wave_incl_scan(v[u], lane);
         v[u] = inc - v[u];
       }
@@ -648,10 +649,9 @@ __device__ __forceinline__ void bin_scatter_scan_body(const BinScatterArgs& sa, 
       if (u >= nu) break;
       const int k = u * NW + wv;  // exclusive sum of the waves before this one
       const int e = __builtin_amdgcn_readlane(u < NB / 2 ? s0 - p0 : s1 - p1, k & 63);
-      const int b = min(b0 + t + u * kBinThreads, T);
-      sh[b] = (unsigned)(b < T ? carry + e + v[u] + o[u] : o[u]);
+      const int b = min(t + u * kBinThreads, T);
+      sh[b] = (unsigned)(b < T ? e + v[u] + o[u] : o[u]);
     }
-    carry += __builtin_amdgcn_readlane(s1, 63);
     __syncthreads();
   }
   for (int64_t jb = j0; jb < j1; jb += kBinThreads * kBinBatch) {
@@ -1563,7 +1563,7 @@ static BinScatterArgs scatter_args(const double* x, const double* y, int64_t M, 
   return a;
 }
 
-bool bin_scan_in_scatter(int T) { return (T + 1) * 4 <= kScatterCursorBytes; }
+bool bin_scan_in_scatter(int T) { return T < kScanPerThread * kBinThreads; }
 
 hipError_t launch_bin_scatter_scan(const double* x, const double* y, int64_t M, BinGeom g, int ppw, int G,
                                    const int* off, int* total, const BinScanOut& so, BinRec* recs, int* rej_end,
