@@ -171,8 +171,9 @@ struct InterpArgs {
 // points, point [b][a] at (cx + (a - nx/2) pitch, cy + (b - ny/2) pitch)
 // metres (integer division).  Its fine-grid taps follow the same rule as a
 // binned point's (tau = 2 x inv_g + tau0 as in BinGeom, first tap
-// ceil(tau - w/2)), so the separable kernels apply the weights the generic
-// spreading and interpolation would.
+// ceil(tau - w/2)), so the separable kernels apply the weights of the binned
+// spreading, and of the binned interpolation up to float32 rounding (which
+// forms them with fewer operations, es_weights).
 struct GridPts {
   int nx, ny;
   double pitch, cx, cy;
@@ -212,7 +213,7 @@ hipError_t launch_spread(int w, bool small_chunks, const SpreadArgs& a, int grid
 hipError_t launch_spread_mfma(int w, int tile, const SpreadArgs& a, int grid, hipStream_t st);
 hipError_t launch_spread_reduce(const SpreadReduceArgs& a, int grid, hipStream_t st);
 hipError_t launch_interp(int w, int tile, const InterpArgs& a, int grid, hipStream_t st);
-// separable interpolation at a grid: support (L x L) -> R (nrows x nx) -> out (ny x nx)
+// separable interpolation at a grid: support (L x L) -> out (ny x nx)
 hipError_t launch_grid_interp(int w, const float2* fine, float2* out, const GridPts& p, hipStream_t st);
 // separable spreading of grid values (ny x nx) -> S (ny x L) -> support (L x L)
 hipError_t launch_grid_spread(int w, const float2* vals, float2* S, float2* fine, const GridPts& p, hipStream_t st);

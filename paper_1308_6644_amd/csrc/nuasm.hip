@@ -671,7 +671,8 @@ void set_tile(nuasm_plan_s* pl, int tile) {
 // plans cut the bins finer: down to one sub-batch (two for up to 8192 points,
 // where the launch that sums split bins costs more, 3.4 us, than the second
 // sub-batch, 2.1), but never to more than 2047 possible partial tiles
-// (8 M / chunk), the bound that an allocation-free execute has to meet.  Above 458 000 points that is the default size.
+// (8 M / chunk), the bound that an allocation-free execute has to meet.  Above
+// 458 000 points that is the default size.
 // Interpolation likewise, down to 512 records and at most 1024 chunks.  Plans
 // on a caller's workspace keep the default sizes their capacity was computed
 // from, and so do deterministic plans (their sums follow the chunks), the
@@ -825,7 +826,9 @@ int multi_grid(const nuasm_plan_s* pl, const PointSet& q) {
 // accepted points, at most four each, never reach them).
 int* rej_end(const PointSet& q) { return reinterpret_cast<int*>(q.recs + 4 * q.rec_cap); }
 
-// Coordinate normalisation and binning of one point set (three launches).
+// Coordinate normalisation and binning of one point set: one launch for small
+// sets, else three, or four where the scan of the bin totals is a launch of its
+// own (deterministic mode, 16641 bins or more, stage timing, no points).
 nuasm_status bind_points(nuasm_plan_s* pl, PointSet& q, int64_t M, const double* x, const double* y) {
   if (M < 0) return fail(NUASM_ERR_INVALID_ARG, "M < 0");
   if (M > 0 && (!x || !y)) return fail(NUASM_ERR_INVALID_ARG, "coordinate pointer is NULL");
