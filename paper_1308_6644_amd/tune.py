@@ -2,8 +2,9 @@
 
 What it searches, per plane class (operator type, N, kernel width w,
 transfer function, log2 of the point count):
-  * spread_chunk      -- records per spreading workgroup (1792 or the small size),
-  * interp_chunk      -- records per interpolation workgroup (1024 .. 8192),
+  * spread_chunk      -- records per spreading workgroup (automatic, which follows
+                         the point count, or the small size),
+  * interp_chunk      -- records per interpolation workgroup (automatic or 1024 .. 8192),
   * bin_range_points  -- points per binning workgroup (automatic or 4096 .. 65535),
   * spread_method     -- spreading on the matrix cores or by register gather,
   * bin_tile          -- bin side, 32 or 64 fine cells (64: fewer duplicated
