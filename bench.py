@@ -564,11 +564,12 @@ def nuasm3_workload(a, torch, P, d):
 
 # Rayleigh-Sommerfeld direct summation: floating-point operations per source
 # / destination pair as the kernel evaluates Eq. 10 up to |z|/lambda = 1e5, the
-# timed distance's form (an FMA counts two): float64 18 (differences,
-# 1 + rho^2/z^2, its root by one residual correction, the phase and its
-# reduction), float32 19 (amplitude, complex products, accumulation), and the
-# three hardware estimates (rsq, sin, cos) one each.
-RS_FLOPS_PER_PAIR = 18 + 19 + 3
+# timed distance's form (an FMA counts two): float64 20 (differences,
+# rho^2 + z^2, the path difference and its residual correction, the phase and
+# its reduction), float32 22 (the correction's square, amplitude, complex
+# products, accumulation), and the three hardware estimates (rsq, sin, cos) one
+# each.
+RS_FLOPS_PER_PAIR = 20 + 22 + 3
 # Vector ALU ceiling for that mix: float64 FMA and non-packed float32 FMA
 # issue at the same rate, 256 CUs x 64 lanes x 2 flops x 2.4 GHz.
 ALU_PEAK_TFLOPS = 78.6
@@ -577,7 +578,7 @@ PAPER_RS_S, PAPER_NUASM1_MS = 76.0, 46.0  # the paper's CPU times at N = 256 (co
 # SQ_INSTS_VALU / (pairs / 64), profiles/rs_direct_paper_N256.md), and the
 # issue ceiling: 256 CUs x 4 SIMDs, one wave64 VALU instruction per SIMD every
 # 4 cycles at 2.4 GHz
-RS_VALU_PER_PAIR = 31.3
+RS_VALU_PER_PAIR = 34.3
 VALU_ISSUE_PER_S = 256 * 4 * 2.4e9 / 4
 
 
