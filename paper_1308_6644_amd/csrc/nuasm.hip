@@ -774,12 +774,13 @@ int64_t scratch_tiles_most(const nuasm_plan_s* pl, const PointSet& q) {
 
 // Partial tiles for the bound set.  They are allocated for every set up to the
 // record buffer's capacity where only a bound of the need is known (16.8 MB
-// from 65504 points on, 8 KB a tile), and with a quarter to spare where the
-// count is exact, so that a new set of points seldom or never allocates.
+// from 65504 points on, 8 KB a tile); where the count is exact, for it, and with
+// a quarter to spare when they grow, so that new sets of points seldom do.
 nuasm_status ensure_scratch(nuasm_plan_s* pl, PointSet& q) {
   int64_t need = std::max<int64_t>(scratch_tiles_needed(pl, q), 1);
   if (q.scratch && need <= q.scratch_chunks) return NUASM_OK;
-  need = std::max(need, q.synced ? std::min(need + need / 4, scratch_tiles_most(pl, q)) : scratch_tiles_most(pl, q));
+  if (!q.synced) need = std::max(need, scratch_tiles_most(pl, q));
+  else if (q.scratch) need = std::max(need, std::min(need + need / 4, scratch_tiles_most(pl, q)));
   // a workspace holds the bound for its capacity, which covers every M <= it
   if (pl->ws) return fail(NUASM_ERR_INVALID_ARG, "split-bin scratch exceeds the workspace");
   if (q.scratch) {
