@@ -404,20 +404,21 @@ nuasm_status nuasm_batch_create(int32_t P, const nuasm_params* params, void* hip
 nuasm_status nuasm_batch_destroy(nuasm_batch batch);  /* NULL-safe */
 /* One-shot run of every plane p: bin M[p] points x[p], y[p] (device FP64
  * metres) and apply the operator to in[p] -> out[p] (device complex64, shapes
- * as for nuasm_execute).  The first call with a given set of pointers and
- * counts records the graph (and runs it); later calls with the same arguments
- * only launch it.  Never synchronises the host then.  In the grouped form a
- * call with other buffers but the same counts keeps the recorded graph: it
- * waits for the graph's last run, rewrites the per-stage argument tables and
- * launches (any other change records the graph again). */
+ * as for nuasm_execute).  The first call records the graph (and runs it); later
+ * calls with the same arguments only launch it.  Never synchronises the host
+ * then.  In the grouped form a call with other buffers but the same counts keeps
+ * the recorded graph: it waits for the graph's last run, rewrites the per-stage
+ * argument tables and launches.  A call with any other change runs the planes
+ * one after the other, without a graph; the same arguments a second time in a
+ * row are recorded in the old graph's place. */
 nuasm_status nuasm_batch_run(nuasm_batch batch, const int64_t* M, const double* const* x,
                              const double* const* y, const void* const* in, void* const* out);
 /* The same work in two steps, for many operator runs on points bound once
  * (the iterations of a hologram optimisation over many planes): binning of
  * every plane's points (M[p], x[p], y[p] as above), recorded as one graph on
  * first use, then the operators of every plane (in[p] -> out[p]) recorded as
- * another.  Each graph is recorded again only when its arguments change
- * (execute_many's also when a plane's point count changed).  execute_many
+ * another.  Each graph is kept, and recorded again, as nuasm_batch_run's
+ * (execute_many's arguments include the planes' point counts).  execute_many
  * returns NUASM_ERR_NOT_READY until every plane has points (and again after
  * nuasm_batch_set_tuning).  Never synchronise the host once recorded. */
 nuasm_status nuasm_set_points_many(nuasm_batch batch, const int64_t* M, const double* const* x,
@@ -452,9 +453,9 @@ nuasm_status nuasm_batch_check_points(nuasm_batch batch, int32_t* bad_plane);
  * drops the recorded graphs. */
 nuasm_status nuasm_batch_set_plane_times(nuasm_batch batch, int32_t enabled);
 /* Synchronise; ms[p] = device wall-clock time from the start of the last
- * recorded-graph launch (run, set_points_many or execute_many) to the
- * completion of plane p (caller-owned host array of P floats).  A plane with
- * no launch (no points, type 2 with nothing to do) completes at 0.
+ * call (run, set_points_many or execute_many) to the completion of plane p
+ * (caller-owned host array of P floats).  In a recorded graph a plane with no
+ * launch (no points, type 2 with nothing to do) completes at 0.
  * NUASM_ERR_NOT_READY when stamps are off or no recorded graph has run since
  * the graphs were last dropped. */
 nuasm_status nuasm_batch_plane_times(nuasm_batch batch, float* ms);

@@ -1856,6 +1856,7 @@ struct BatchGraph {
   std::vector<int64_t> M;    // the point counts it was recorded with
   std::vector<uint64_t> buffers;  // its planes' buffer generations (nuasm_plan_s::buffers) then
   std::vector<BoundPoints> bound;  // per plane, if the graph binds points: a replay binds them again
+  std::vector<const void*> plain_key;  // the arguments of the last call, if that ran plainly
   std::vector<int> slot_of;  // plane -> its completion stamp in ts (0: finished at the start)
 };
 
@@ -1874,6 +1875,7 @@ struct nuasm_batch_s {
   bool stamps = true;          // completion stamps recorded (nuasm_batch_set_plane_times)
   long long* ts = nullptr;     // [P + 1] device wall-clock stamps: the start, then completions
   const BatchGraph* last = nullptr;  // the graph launched last
+  bool last_plain = false;           // its call ran plainly: plane p's stamp is in slot 1 + p
   int clock_khz = 0;
   int64_t recorded = 0, refreshed = 0;  // graph recordings; grouped tables rewritten in place
 };
@@ -1893,6 +1895,7 @@ void drop_graph(BatchGraph& g) {
   g.M.clear();
   g.buffers.clear();
   g.bound.clear();
+  g.plain_key.clear();
   g.slot_of.clear();
   g.grouped = false;
 }
@@ -2094,11 +2097,17 @@ static hipError_t enqueue_chains(nuasm_batch_s* b, BatchGraph& g, const int* ord
   return e;
 }
 
-// Launch graph g, or record it first when it is missing or was recorded with
-// other arguments (key) or other buffers of its planes: the three graphs of a
-// batch share these, and a run of one of them with more points (or with fewer,
-// whose smaller chunks need more partial tiles) may have moved what another
-// one's launches point to.  plane(pl, p) enqueues plane p's work on the plan's
+// Launch graph g, or record it first when it is missing.  With other arguments
+// (key) than it was recorded with, or other buffers of its planes, it is not
+// replayed: the three graphs of a batch share the buffers, and a run of one of
+// them with more points (or with fewer, whose smaller chunks need more partial
+// tiles) may have moved what another one's launches point to.  A grouped graph
+// whose counts are the same then gets new tables; else the call runs plainly,
+// plane after plane, and the graph stays, until the same arguments come a
+// second time in a row: those are recorded in its place.  So arguments that
+// change from call to call cost no recording each, and no run drops a graph
+// that the run before launched.  (Of the runs that did, per-plane form, one
+// ended in an abort on the host; the cause was not found.)  plane(pl, p) enqueues plane p's work on the plan's
 // current stream.  Recording: one eager pass on the caller's stream (sizes every
 // buffer and sets kernel attributes, so that the capture enqueues launches
 // only), then the capture on the internal stream -- stamp, fork onto the
@@ -2114,6 +2123,8 @@ static nuasm_status batch_launch(nuasm_batch_s* b, BatchGraph& g, bool binds, co
     // on the caller's stream itself: ordered with its other work, no event
     // hops between streams
     b->last = &g;
+    b->last_plain = false;
+    g.plain_key.clear();
     HIP_TRY(hipGraphLaunch(g.exec, b->stream), "hipGraphLaunch");
     for (size_t p = 0; p < g.bound.size(); ++p) {
       PointSet& q = b->plans[p]->ps[0];
@@ -2149,18 +2160,37 @@ static nuasm_status batch_launch(nuasm_batch_s* b, BatchGraph& g, bool binds, co
       return launch();
     }
   }
+  // every plane's own launches on the caller's stream, with or without stamps
+  auto run_planes = [&](bool stamps) -> nuasm_status {
+    if (stamps) HIP_TRY(launch_stamp(b->ts, b->stream), "launch stamp");
+    for (int p = 0; p < P; ++p) {
+      nuasm_plan_s* pl = b->plans[p];
+      pl->stream = b->stream;
+      pl->timing = false;
+      nuasm_status s = plane(pl, p);
+      if (s != NUASM_OK) return fail(s, "plane " + std::to_string(p) + ": " + g_last_error);
+      if (stamps) HIP_TRY(launch_stamp(b->ts + 1 + p, b->stream), "launch stamp");
+    }
+    return NUASM_OK;
+  };
+  if (g.exec && key != g.plain_key) {
+    g.plain_key.clear();
+    const nuasm_status s = run_planes(b->stamps);
+    if (s != NUASM_OK) return s;
+    b->last = &g;
+    b->last_plain = true;
+    g.plain_key = key;
+    return NUASM_OK;
+  }
   if (g.exec || g.tables) {
     HIP_TRY(hipStreamSynchronize(b->stream), "hipStreamSynchronize");
     drop_graph(g);
   }
-  // eager pass on the caller's stream: sizes every buffer and sets kernel
-  // attributes, so that the capture below enqueues launches only
-  for (int p = 0; p < P; ++p) {
-    nuasm_plan_s* pl = b->plans[p];
-    pl->stream = b->stream;
-    pl->timing = false;
-    nuasm_status s = plane(pl, p);
-    if (s != NUASM_OK) return fail(s, "plane " + std::to_string(p) + ": " + g_last_error);
+  // eager pass: sizes every buffer and sets kernel attributes, so that the
+  // capture below enqueues launches only
+  {
+    const nuasm_status s = run_planes(false);
+    if (s != NUASM_OK) return s;
   }
   HIP_TRY(hipStreamSynchronize(b->stream), "hipStreamSynchronize");
   if (b->grouped) {
@@ -2451,7 +2481,10 @@ nuasm_status nuasm_batch_plane_times(nuasm_batch b, float* ms) {
   std::vector<long long> h(P + 1);
   HIP_TRY(hipMemcpy(h.data(), b->ts, sizeof(long long) * (P + 1), hipMemcpyDeviceToHost), "hipMemcpy");
   const std::vector<int>& slot = b->last->slot_of;
-  for (size_t p = 0; p < P; ++p) ms[p] = (float)((double)(h[slot[p]] - h[0]) / (double)b->clock_khz);
+  for (size_t p = 0; p < P; ++p) {
+    const size_t at = b->last_plain ? 1 + p : (size_t)slot[p];
+    ms[p] = (float)((double)(h[at] - h[0]) / (double)b->clock_khz);
+  }
   return NUASM_OK;
 }
 
